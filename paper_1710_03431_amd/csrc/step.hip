@@ -79,6 +79,8 @@ struct StepArgs {
   int M_run;             // grid points processed (M, or fewer when autotuning)
   int NP, TQ;            // padded levels and column tiles of this instance (batched runs)
   int64_t tiles;         // workgroup tiles of this instance
+  int64_t t_base;        // first trajectory of this launch and its first row of `partial`
+  int64_t tile0;         // (a run may take several launches of different tile widths)
   double* pgs_sum;       // [M] (batched runs reduce into these)
   double* pgs_sumsq;
   const double* tbeg;    // [M] start time of the step into grid g
@@ -158,11 +160,16 @@ __device__ __forceinline__ void split4(const float* x, s16x4& hi, s16x4& lo) {
   lo = __builtin_bit_cast(s16x4, make_uint2(l[0], l[1]));
 }
 
-// One A-operand fragment of Delta (per lane): a value for the K = 4 MFMAs,
-// hi/lo BF16 words for the K = 16 and K = 32 ones.
+// A-operand fragments of Delta read by one load per lane: 16 bytes of consecutive k
+// chunks for the K = 4 MFMAs (frag_chunks of them), hi/lo BF16 words of one chunk for
+// the K = 16 and K = 32 ones.
+template <class Mode>
+constexpr int frag_chunks() {
+  return Mode::KC == 4 ? static_cast<int>(16 / sizeof(typename Mode::T)) : 1;
+}
 template <class Mode>
 struct Frag {
-  typename Mode::T v;
+  typename Mode::T v __attribute__((ext_vector_type(frag_chunks<Mode>())));
 };
 template <>
 struct Frag<ModeBF16K16> {
@@ -177,7 +184,7 @@ template <class Mode>
 __device__ __forceinline__ Frag<Mode> load_frag(const StepArgs& a, size_t idx) {
   Frag<Mode> f;
   if constexpr (Mode::KC == 4) {
-    f.v = static_cast<const typename Mode::T*>(a.dlt_a)[idx];
+    f = static_cast<const Frag<Mode>*>(a.dlt_a)[idx];
   } else if constexpr (Mode::KC == 16) {
     f.h = static_cast<const uint2*>(a.dlt_a)[idx];
     f.l = static_cast<const uint2*>(a.dlt_b)[idx];
@@ -188,14 +195,18 @@ __device__ __forceinline__ Frag<Mode> load_frag(const StepArgs& a, size_t idx) {
   return f;
 }
 
-// Chunks of A fragments kept in flight: a ring of PF chunks per unit, refilled
-// PF chunks ahead and, at the end of a step, with the first chunks of the next
-// step, so the loads overlap the epilogue and the jump handler.
+// Loads of A fragments kept in flight: a ring of PF loads per unit, refilled
+// PF loads ahead and, at the end of a step, with the first ones of the next
+// step, so the loads overlap the epilogue and the jump handler.  A row of Delta is
+// latency-bound L2 traffic, so the loads are 16 bytes a lane (4-byte loads of single
+// chunks: 256 levels FP32, a step of an 8-trajectory tile 12.0 us against 9.9, of a
+// 16-trajectory tile 31.4 us against 14.4); rings of 2, 4 and 8 such loads measured
+// 14.4, 14.5 and 14.6 us there and 28.0, 27.5 and 28.7 us with 40 trajectories.
 template <class Mode, int NP>
 constexpr int prefetch_depth() {
-  constexpr int NKC = NP / Mode::KC;
-  constexpr int want = (Mode::KC == 4) ? 8 : 2;
-  return NKC < want ? NKC : want;
+  constexpr int NKG = NP / Mode::KC / frag_chunks<Mode>();
+  constexpr int want = (Mode::KC == 4) ? 4 : 2;
+  return NKG < want ? NKG : want;
 }
 
 // ----------------------------------------------------------- jump handler --
@@ -829,6 +840,8 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
   constexpr int NUNITS = NRT * (TQ / QG);
   constexpr int UPW = (NUNITS + WV - 1) / WV;      // units per wave
   constexpr int NKC = NP / Mode::KC;
+  constexpr int FW = frag_chunks<Mode>();   // k chunks per fragment load
+  constexpr int NKG = NKC / FW;
   static_assert(TT <= kWave, "tile must fit one wavefront for the decision pass");
 
   auto& S = sh.S;
@@ -843,7 +856,7 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform per wave
-  const int64_t tb = tile * TT;
+  const int64_t tb = a.t_base + tile * TT;
   const int lc = lane & 15;          // MFMA output column
   const int part = (lane >> 3) & 1;  // 0: real part, 1: imaginary part
 
@@ -875,14 +888,14 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
   constexpr bool kSharedQ = (NRT >= WV);
   static_assert(NSLOT == (kSharedQ ? WV : NRT), "norm slots follow the work split");
 #define q0(u) (kSharedQ ? 0 : q0_u[u])
-  // fragment (g, row tile, k chunk) lives at ((g * NRT + rt) * NKC + k) * 64 + lane
+  // fragment load (g, row tile, k group) lives at ((g * NRT + rt) * NKG + k) * 64 + lane
   size_t fbase[UPW];
 #pragma unroll
-  for (int u = 0; u < UPW; ++u) fbase[u] = static_cast<size_t>(rt_u[u]) * NKC * kWave + lane;
+  for (int u = 0; u < UPW; ++u) fbase[u] = static_cast<size_t>(rt_u[u]) * NKG * kWave + lane;
 #define frag_index(gg, u, k) \
-  (static_cast<size_t>(gg) * (NRT * NKC * kWave) + fbase[u] + static_cast<size_t>(k) * kWave)
+  (static_cast<size_t>(gg) * (NRT * NKG * kWave) + fbase[u] + static_cast<size_t>(k) * kWave)
   constexpr int PF = prefetch_depth<Mode, NP>();
-  static_assert(NKC % PF == 0, "prefetch depth must divide the k chunks");
+  static_assert(NKG % PF == 0, "prefetch depth must divide the k groups");
   Frag<Mode> ring[PF][UPW];
   if (a.M_run > 2) {
 #pragma unroll
@@ -993,50 +1006,56 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
       // equal priorities, and wave 0 one level higher still another 0.6% in FP32.
       if (WV == 8 && wave == 0) __builtin_amdgcn_s_setprio(2);
       else if (WV == 8 && wave < 4) __builtin_amdgcn_s_setprio(1);
-      for (int kc = 0; kc < NKC; kc += PF) {
+      for (int kg = 0; kg < NKG; kg += PF) {
 #pragma unroll
         for (int s2 = 0; s2 < PF; ++s2) {
-          const int k = kc + s2;
           Frag<Mode> av[UPW];
 #pragma unroll
           for (int u = 0; u < UPW; ++u) av[u] = ring[s2][u];
-          // refill this slot PF chunks ahead (next step's first chunks at the end)
+          // refill this slot PF loads ahead (next step's first ones at the end)
           // (after the last step the slot reloads grid M_run - 1: in bounds, unused)
-          const int kn = k + PF;
-          const int gn = min(kn < NKC ? g : g + 1, a.M_run - 1);
-          const int kk = kn < NKC ? kn : kn - NKC;
+          const int kn = kg + s2 + PF;
+          const int gn = min(kn < NKG ? g : g + 1, a.M_run - 1);
+          const int kk = kn < NKG ? kn : kn - NKG;
 #pragma unroll
           for (int u = 0; u < UPW; ++u)
             if (ok_u[u]) ring[s2][u] = load_frag<Mode>(a, frag_index(gn, u, kk));
           if constexpr (Mode::KC == 4 && kSharedQ) {
             // B for this chunk was read one chunk ahead; read the next one now (on
             // the last chunk that is padding row NP + lane / 16: in bounds, unused)
-            T bcur[QG];
 #pragma unroll
-            for (int qq = 0; qq < QG; ++qq) bcur[qq] = bnx[qq];
-            const int krn = 4 * (k + 1) + (lane >> 4);
+            for (int w = 0; w < FW; ++w) {
+              const int k = (kg + s2) * FW + w;
+              T bcur[QG];
 #pragma unroll
-            for (int qq = 0; qq < QG; ++qq) bnx[qq] = S[qq][lc][krn];
+              for (int qq = 0; qq < QG; ++qq) bcur[qq] = bnx[qq];
+              const int krn = 4 * (k + 1) + (lane >> 4);
 #pragma unroll
-            for (int u = 0; u < UPW; ++u)
+              for (int qq = 0; qq < QG; ++qq) bnx[qq] = S[qq][lc][krn];
 #pragma unroll
-              for (int qq = 0; qq < QG; ++qq) acc[u][qq] = mfma_k4(av[u].v, bcur[qq], acc[u][qq]);
+              for (int u = 0; u < UPW; ++u)
+#pragma unroll
+                for (int qq = 0; qq < QG; ++qq) acc[u][qq] = mfma_k4(av[u].v[w], bcur[qq], acc[u][qq]);
+            }
           } else if constexpr (Mode::KC == 4) {
-            const int krow = 4 * k + (lane >> 4);
-            T bv[UPW][QG];
 #pragma unroll
-            for (int u = 0; u < UPW; ++u)
+            for (int w = 0; w < FW; ++w) {
+              const int krow = 4 * ((kg + s2) * FW + w) + (lane >> 4);
+              T bv[UPW][QG];
 #pragma unroll
-              for (int qq = 0; qq < QG; ++qq)
-                bv[u][qq] = (u == 0 || !kSharedQ) ? S[q0(u) + qq][lc][krow] : bv[0][qq];
+              for (int u = 0; u < UPW; ++u)
 #pragma unroll
-            for (int u = 0; u < UPW; ++u) {
-              if (!ok_u[u]) continue;
+                for (int qq = 0; qq < QG; ++qq)
+                  bv[u][qq] = (u == 0 || !kSharedQ) ? S[q0(u) + qq][lc][krow] : bv[0][qq];
 #pragma unroll
-              for (int qq = 0; qq < QG; ++qq) acc[u][qq] = mfma_k4(av[u].v, bv[u][qq], acc[u][qq]);
+              for (int u = 0; u < UPW; ++u) {
+                if (!ok_u[u]) continue;
+#pragma unroll
+                for (int qq = 0; qq < QG; ++qq) acc[u][qq] = mfma_k4(av[u].v[w], bv[u][qq], acc[u][qq]);
+              }
             }
           } else if constexpr (Mode::KC == 16) {
-            const int k0 = 16 * k + 4 * (lane >> 4);
+            const int k0 = 16 * (kg + s2) + 4 * (lane >> 4);
 #pragma unroll
             for (int u = 0; u < UPW; ++u) {
               if (!ok_u[u]) continue;
@@ -1056,7 +1075,7 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
               }
             }
           } else {
-            const int k0 = 32 * k + 8 * (lane >> 4);
+            const int k0 = 32 * (kg + s2) + 8 * (lane >> 4);
             // B split once per column tile when every unit shares the column tiles
             bf16x8 bh[kSharedQ ? QG : 1], bl[kSharedQ ? QG : 1];
             if constexpr (kSharedQ) {
@@ -1229,7 +1248,7 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
       const double sp = seg_sum<64>(p);
       const double sq = seg_sum<64>(p * p);
       if (lane == 0) {
-        double* dst = a.partial + (static_cast<size_t>(tile) * a.M + g) * 2;
+        double* dst = a.partial + (static_cast<size_t>(a.tile0 + tile) * a.M + g) * 2;
         dst[0] = sp;
         dst[1] = sq;
       }
@@ -1292,19 +1311,38 @@ struct CompSum {
   __device__ double value() const { return s + c; }
 };
 
-__global__ void k_reduce_partials(const double* __restrict__ partial, int64_t tiles, int M, double K,
-                                  double* __restrict__ sum, double* __restrict__ sumsq) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= M) return;
-  double s = 0.0, q = 0.0;
-  if (g == 0) {
-    s = K;   // every trajectory starts in the ground state of H(0)
-    q = K;
-  } else {
-    CompSum cs, cq;
-    for (int64_t t = 0; t < tiles; ++t) {
-      cs.add(partial[(t * M + g) * 2]);
-      cq.add(partial[(t * M + g) * 2 + 1]);
+// Sums of the per-tile observables of one run over its tiles.  A workgroup takes kRedG
+// consecutive grid points (one 256-byte row segment of `partial` per tile) and splits the
+// tiles over kRedT threads per grid point, each with its own compensated sums, which are
+// then added in thread order: with one thread per grid point a run of 1563 tiles and 500
+// points waited 460 us for its loads on two workgroups; this takes 37 us.
+constexpr int kRedG = 16, kRedT = 16;
+__device__ void reduce_tiles(const double* __restrict__ partial, int64_t tiles, int M, double K,
+                             double* __restrict__ sum, double* __restrict__ sumsq) {
+  __shared__ double part[kRedT][kRedG][4];
+  const int gl = threadIdx.x % kRedG, tl = threadIdx.x / kRedG;
+  const int g = blockIdx.x * kRedG + gl;
+  CompSum cs, cq;
+  if (g > 0 && g < M) {
+    for (int64_t t = tl; t < tiles; t += kRedT) {
+      const double2 v = *reinterpret_cast<const double2*>(partial + (t * M + g) * 2);
+      cs.add(v.x);
+      cq.add(v.y);
+    }
+  }
+  part[tl][gl][0] = cs.s;
+  part[tl][gl][1] = cs.c;
+  part[tl][gl][2] = cq.s;
+  part[tl][gl][3] = cq.c;
+  __syncthreads();
+  if (tl || g >= M) return;
+  double s = K, q = K;   // g = 0: every trajectory starts in the ground state of H(0)
+  if (g > 0) {
+    for (int k = 1; k < kRedT; ++k) {
+      cs.add(part[k][gl][0]);
+      cs.c += part[k][gl][1];
+      cq.add(part[k][gl][2]);
+      cq.c += part[k][gl][3];
     }
     s = cs.value();
     q = cq.value();
@@ -1313,12 +1351,18 @@ __global__ void k_reduce_partials(const double* __restrict__ partial, int64_t ti
   if (sumsq) sumsq[g] = q;
 }
 
+__global__ __launch_bounds__(kRedG * kRedT) void k_reduce_partials(const double* __restrict__ partial, int64_t tiles,
+                                                                   int M, double K, double* __restrict__ sum,
+                                                                   double* __restrict__ sumsq) {
+  reduce_tiles(partial, tiles, M, K, sum, sumsq);
+}
+
 // Column-tile counts instantiated per level count and precision.
-constexpr int kTQ[] = {1, 2, 4, 5, 8};
+constexpr int kTQ[] = {1, 2, 3, 4, 5, 8};
 
 __host__ __device__ constexpr bool tq_allowed(int NP, int TQ, bool f64) {
-  return (NP <= 64) ? (TQ != 5 && !(f64 && NP == 64 && TQ == 8))
-                    : (TQ <= 5 && !(f64 && TQ > 2));
+  return (NP <= 64) ? (TQ != 3 && TQ != 5 && !(f64 && NP == 64 && TQ == 8))
+                    : (TQ <= 5 && !(f64 && TQ > 4));
 }
 
 // ------------------------------------------------------------- batched ----
@@ -1369,25 +1413,9 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<NP, BatchMode<NP, Mode>>()
   }
 }
 
-__global__ void k_reduce_batch(const StepArgs* __restrict__ args) {
+__global__ __launch_bounds__(kRedG * kRedT) void k_reduce_batch(const StepArgs* __restrict__ args) {
   const StepArgs& a = args[blockIdx.y];
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= a.M) return;
-  double s = 0.0, q = 0.0;
-  if (g == 0) {
-    s = static_cast<double>(a.K);
-    q = s;
-  } else {
-    CompSum cs, cq;
-    for (int64_t t = 0; t < a.tiles; ++t) {
-      cs.add(a.partial[(t * a.M + g) * 2]);
-      cq.add(a.partial[(t * a.M + g) * 2 + 1]);
-    }
-    s = cs.value();
-    q = cq.value();
-  }
-  if (a.pgs_sum) a.pgs_sum[g] = s;
-  if (a.pgs_sumsq) a.pgs_sumsq[g] = q;
+  reduce_tiles(a.partial, a.tiles, a.M, static_cast<double>(a.K), a.pgs_sum, a.pgs_sumsq);
 }
 
 template <class Mode, int NP>
@@ -1401,7 +1429,7 @@ hipError_t launch_tq(int TQ, const StepArgs& a, int64_t blocks, hipStream_t st) 
       return hipGetLastError();                                                               \
     }                                                                                         \
   }
-  AQT_CASE(1) AQT_CASE(2) AQT_CASE(4) AQT_CASE(5) AQT_CASE(8)
+  AQT_CASE(1) AQT_CASE(2) AQT_CASE(3) AQT_CASE(4) AQT_CASE(5) AQT_CASE(8)
 #undef AQT_CASE
   return hipErrorInvalidValue;
 }
@@ -1422,70 +1450,111 @@ hipError_t launch_mode(int NP, int TQ, const StepArgs& a, int64_t blocks, hipStr
 
 }  // namespace
 
-// Column tiles per workgroup: minimise the largest per-CU load
-// ceil(workgroups / CUs) * TQ (every workgroup does the same work per
-// trajectory-step), preferring larger tiles on ties (fewer overlap re-reads).
-// Trajectories per workgroup (TQ column tiles of 8).  >= 128 levels: one workgroup per
-// CU, so the launch takes ceil(workgroups / CUs) rounds, each costing the measured
-// time of one tile of that width (relative units, n = 256 on MI355X; wider tiles
-// amortise the overlap operand over more trajectories).  Smaller level counts fit
-// several workgroups per CU: the widest tile that still gives every CU a workgroup.
-int choose_tq(int NP, int precision, int64_t K, int cus) {
-  const int64_t tiles8 = (K + 7) / 8;
+namespace {
+
+// Launches of one run: widths (column tiles of 8 trajectories per workgroup) and
+// workgroups, widest first.
+struct TilePlan {
+  int n = 0;
+  int tq[8];
+  int64_t wgs[8];
+  int64_t tiles() const {
+    int64_t t = 0;
+    for (int i = 0; i < n; ++i) t += wgs[i];
+    return t;
+  }
+  void add(int w, int64_t count) {
+    tq[n] = w;
+    wgs[n++] = count;
+  }
+};
+
+// Width of the explicit `tile` parameter (trajectories per workgroup); 0 if unsupported.
+int explicit_tq(int NP, int precision, int tile) {
+  const int tq = tile / 8;
   const bool f64 = precision == AQT_FP64;
+  if (tile % 8 || !(tq == 1 || tq == 2 || tq == 4 || tq == 5 || tq == 8)) return 0;
+  if (NP > 64 && f64 && tq > 2) return 0;   // 24 and 32 are chosen by plan_tiles only
+  return tq_allowed(NP, tq, f64) ? tq : 0;
+}
+
+// Split of K trajectories over the chip.  Up to 64 levels several workgroups share a CU:
+// one launch with the widest tile that still gives every CU a workgroup.  Above, a CU holds
+// one workgroup, so a launch takes rounds of one tile per CU and a round costs the step
+// time of its width whether or not the CUs are full: the run is cut into the cheapest set
+// of widths whose sum covers the column tiles that fall to each CU.  Step times in
+// 0.1 us, measured at 256 levels on the 2000-point anneal: FP64 rises linearly (the GEMM
+// binds), so what counts is not to pay for idle columns: 10^4 trajectories (4.9 columns a
+// CU) take 3 + 2 (51.4 us a step) instead of three rounds of 2 (61.2); FP32 and BF16 gain
+// from width up to 5 (4096 trajectories on 256 tiles of 16: 13.2 us instead of 19.7 on 128
+// tiles of 32).
+TilePlan plan_tiles(int NP, int precision, int64_t K, int cus) {
+  const int64_t cols = (K + 7) / 8;
+  const bool f64 = precision == AQT_FP64;
+  TilePlan plan;
   if (NP <= 64) {
     int best = 1;
     for (int tq : kTQ)
-      if (tq_allowed(NP, tq, f64) && (tiles8 + tq - 1) / tq >= cus) best = tq > best ? tq : best;
-    return best;
+      if (tq_allowed(NP, tq, f64) && (cols + tq - 1) / tq >= cus) best = tq;
+    plan.add(best, (cols + best - 1) / best);
+    return plan;
   }
-  auto round_cost = [&](int tq) -> int64_t {
-    if (f64) return tq == 1 ? 24 : 43;
-    switch (tq) {   // ms per CU-full round at 256 levels, measured on a 2000-point anneal
-      case 1: return 30;
-      case 2: return 63;
-      case 4: return 41;
-      default: return 50;
-    }
-  };
-  int best = 1;
-  int64_t best_cost = INT64_MAX;
-  for (int tq : kTQ) {
-    if (!tq_allowed(NP, tq, f64)) continue;
-    const int64_t wgs = (tiles8 + tq - 1) / tq;
-    const int64_t cost = ((wgs + cus - 1) / cus) * round_cost(tq);
-    if (cost < best_cost || (cost == best_cost && tq > best)) {
-      best = tq;
-      best_cost = cost;
+  constexpr int kW = 5;
+  static constexpr int kCost[3][kW] = {{117, 204, 310, 404, 1 << 20},   // FP64 (1, 2, 3, 4 columns)
+                                       {82, 132, 164, 197, 244},        // FP32
+                                       {65, 87, 114, 141, 169}};        // BF16
+  const int* cost = kCost[f64 ? 0 : (precision == AQT_FP32 ? 1 : 2)];
+  int widest = 1;
+  for (int w = 1; w <= kW; ++w)
+    if (tq_allowed(NP, w, f64)) widest = w;
+  int64_t per_cu = (cols + cus - 1) / cus;   // columns each CU takes
+  int64_t count[kW + 1] = {};
+  constexpr int kExact = 40;                 // beyond this many columns, widest tiles first
+  if (per_cu > kExact) {
+    count[widest] = (per_cu - kExact + widest - 1) / widest;
+    per_cu -= count[widest] * widest;
+  }
+  int best[kExact + 1] = {0}, with[kExact + 1] = {0};
+  for (int c = 1; c <= per_cu; ++c) {
+    best[c] = INT32_MAX;
+    for (int w = 1; w <= widest; ++w) {
+      const int v = best[c > w ? c - w : 0] + cost[w - 1];
+      if (v <= best[c]) {
+        best[c] = v;
+        with[c] = w;
+      }
     }
   }
-  return best;
+  for (int64_t c = per_cu; c > 0; c -= with[c]) ++count[with[c]];
+  int64_t left = cols;
+  for (int w = widest; w >= 1 && left > 0; --w) {
+    if (!count[w]) continue;
+    const int64_t wgs = std::min<int64_t>(count[w] * cus, (left + w - 1) / w);
+    plan.add(w, wgs);
+    left -= wgs * w;
+  }
+  return plan;
 }
 
-namespace {
-
-// Column tiles per workgroup of a run (explicit or chosen); 0 for an unsupported tile.
-int run_tq(const aqt_ctx* ctx, const aqt_run_params* p) {
-  const int prec = p->precision;
-  const int cus = ctx->cus > 0 ? ctx->cus : 256;
-  const int tq = p->tile ? p->tile / 8 : choose_tq(ctx->NP, prec, p->n_traj, cus);
-  if (p->tile && (p->tile % 8 || !(tq == 1 || tq == 2 || tq == 4 || tq == 5 || tq == 8) ||
-                  !tq_allowed(ctx->NP, tq, prec == AQT_FP64)))
-    return 0;
-  return tq;
+// Plan of a run (explicit or chosen width); empty for an unsupported explicit tile.
+TilePlan run_plan(const aqt_ctx* ctx, const aqt_run_params* p) {
+  if (!p->tile) return plan_tiles(ctx->NP, p->precision, p->n_traj, ctx->cus > 0 ? ctx->cus : 256);
+  TilePlan plan;
+  const int tq = explicit_tq(ctx->NP, p->precision, p->tile);
+  if (tq) plan.add(tq, (p->n_traj + 8 * tq - 1) / (8 * tq));
+  return plan;
 }
 
 // Enqueues the trajectory kernel and the observable reduction with the per-tile sums
 // in `partial` ([tiles][M][2] doubles; every entry g >= 1 is written before it is read).
-aqt_status enqueue_run(aqt_ctx* ctx, const aqt_run_params* p, const aqt_outputs* o, int tq, double* partial) {
+aqt_status enqueue_run(aqt_ctx* ctx, const aqt_run_params* p, const aqt_outputs* o, const TilePlan& plan,
+                       double* partial) {
   const int prec = p->precision;
-  const int64_t TT = 8 * tq;
-  const int64_t tiles = (p->n_traj + TT - 1) / TT;
+  const int64_t tiles = plan.tiles();
   StepArgs a{};
   a.M = ctx->M;
   a.M_run = ctx->M;
   a.NP = ctx->NP;
-  a.TQ = tq;
   a.tiles = tiles;
   a.pgs_sum = o->pgs_sum;
   a.pgs_sumsq = o->pgs_sumsq;
@@ -1524,13 +1593,18 @@ aqt_status enqueue_run(aqt_ctx* ctx, const aqt_run_params* p, const aqt_outputs*
   a.final_state = o->final_state;
   a.flags = ctx->run_flags.as<int>();
 
-  hipError_t e;
-  if (prec == AQT_FP64) e = launch_mode<ModeF64>(ctx->NP, tq, a, tiles, ctx->stream);
-  else if (prec == AQT_FP32) e = launch_mode<ModeF32>(ctx->NP, tq, a, tiles, ctx->stream);
-  else e = launch_mode<ModeBF16>(ctx->NP, tq, a, tiles, ctx->stream);
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < plan.n && e == hipSuccess; ++i) {
+    a.TQ = plan.tq[i];
+    if (prec == AQT_FP64) e = launch_mode<ModeF64>(ctx->NP, a.TQ, a, plan.wgs[i], ctx->stream);
+    else if (prec == AQT_FP32) e = launch_mode<ModeF32>(ctx->NP, a.TQ, a, plan.wgs[i], ctx->stream);
+    else e = launch_mode<ModeBF16>(ctx->NP, a.TQ, a, plan.wgs[i], ctx->stream);
+    a.t_base += 8 * a.TQ * plan.wgs[i];
+    a.tile0 += plan.wgs[i];
+  }
   if (e != hipSuccess) return ctx->fail(AQT_EHIP, std::string("trajectory kernel launch: ") + hipGetErrorString(e));
   if (o->pgs_sum || o->pgs_sumsq) {
-    hipLaunchKernelGGL(k_reduce_partials, dim3((ctx->M + 255) / 256), dim3(256), 0, ctx->stream,
+    hipLaunchKernelGGL(k_reduce_partials, dim3((ctx->M + kRedG - 1) / kRedG), dim3(kRedG * kRedT), 0, ctx->stream,
                        partial, tiles, ctx->M, static_cast<double>(p->n_traj), o->pgs_sum, o->pgs_sumsq);
     e = hipGetLastError();
     if (e != hipSuccess) return ctx->fail(AQT_EHIP, std::string("reduction launch: ") + hipGetErrorString(e));
@@ -1560,12 +1634,11 @@ aqt_status launch_run(aqt_ctx* ctx, const aqt_run_params* p, const aqt_outputs* 
   if (s != AQT_OK) return s;
   s = pack_for_precision(ctx, prec);
   if (s != AQT_OK) return s;
-  const int tq = run_tq(ctx, p);
-  if (!tq) return ctx->fail(AQT_EINVAL, "unsupported tile size for this level count and precision");
-  const int64_t tiles = (p->n_traj + 8 * tq - 1) / (8 * tq);
-  const size_t need = static_cast<size_t>(tiles) * ctx->M * 2 * sizeof(double);
+  const TilePlan plan = run_plan(ctx, p);
+  if (!plan.n) return ctx->fail(AQT_EINVAL, "unsupported tile size for this level count and precision");
+  const size_t need = static_cast<size_t>(plan.tiles()) * ctx->M * 2 * sizeof(double);
   if (ctx->partial.reserve(need) != hipSuccess) return ctx->fail(AQT_ENOMEM, "workspace allocation failed");
-  return enqueue_run(ctx, p, o, tq, ctx->partial.as<double>());
+  return enqueue_run(ctx, p, o, plan, ctx->partial.as<double>());
 }
 
 aqt_status setup_noalloc_scratch(aqt_ctx* ctx) {
@@ -1596,15 +1669,23 @@ aqt_status launch_run_noalloc(aqt_ctx* ctx, const aqt_run_params* p, const aqt_o
     if (ctx->device >= 0 && ctx->device < kMaxDevices) base = g_scratch_ptr[ctx->device];
   }
   if (!base) return ctx->fail(AQT_ESTATE, "the device scratch buffer has no address (aqt_create did not set it up)");
-  const int tq = run_tq(ctx, p);
-  if (!tq) return ctx->fail(AQT_EINVAL, "unsupported tile size for this level count and precision");
-  const int64_t tiles = (p->n_traj + 8 * tq - 1) / (8 * tq);
-  const double need = static_cast<double>(tiles) * ctx->M * 2 * sizeof(double);
+  TilePlan plan = run_plan(ctx, p);
+  if (!plan.n) return ctx->fail(AQT_EINVAL, "unsupported tile size for this level count and precision");
+  auto bytes = [&]() { return static_cast<double>(plan.tiles()) * ctx->M * 2 * sizeof(double); };
+  if (!p->tile && bytes() > static_cast<double>(kScratchBytes)) {
+    // the widest tile needs the least scratch
+    int w = 1;
+    for (int tq : kTQ)
+      if (tq_allowed(ctx->NP, tq, prec == AQT_FP64)) w = tq;
+    plan = TilePlan();
+    plan.add(w, (p->n_traj + 8 * w - 1) / (8 * w));
+  }
+  const double need = bytes();
   if (need > static_cast<double>(kScratchBytes))
     return ctx->fail(AQT_EINVAL, "the run needs " + std::to_string(static_cast<long long>(need)) +
                                      " bytes of per-tile sums (tiles x n_grid x 16), more than the " +
                                      std::to_string(kScratchBytes) + "-byte no-allocation buffer");
-  return enqueue_run(ctx, p, o, tq, static_cast<double*>(base));
+  return enqueue_run(ctx, p, o, plan, static_cast<double*>(base));
 }
 
 }  // namespace aqt
@@ -2020,7 +2101,7 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
                                  b->capture_stream);
     int maxM = 0;
     for (auto& a : b->hargs) maxM = std::max(maxM, a.M);
-    hipLaunchKernelGGL(k_reduce_batch, dim3((maxM + 255) / 256, n), dim3(256), 0, b->capture_stream,
+    hipLaunchKernelGGL(k_reduce_batch, dim3((maxM + kRedG - 1) / kRedG, n), dim3(kRedG * kRedT), 0, b->capture_stream,
                        b->dargs.as<StepArgs>());
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(b->capture_stream, &g);
@@ -2052,7 +2133,8 @@ aqt_status aqt_batch_launch(aqt_batch* b) {
     return b->fail(AQT_EHIP, "batch launch failed");
   int maxM = 0;
   for (auto& a : b->hargs) maxM = std::max(maxM, a.M);
-  hipLaunchKernelGGL(k_reduce_batch, dim3((maxM + 255) / 256, b->n), dim3(256), 0, b->stream, b->dargs.as<StepArgs>());
+  hipLaunchKernelGGL(k_reduce_batch, dim3((maxM + kRedG - 1) / kRedG, b->n), dim3(kRedG * kRedT), 0, b->stream,
+                     b->dargs.as<StepArgs>());
   if (hipGetLastError() != hipSuccess) return b->fail(AQT_EHIP, "batch reduction launch failed");
   return AQT_OK;
 }

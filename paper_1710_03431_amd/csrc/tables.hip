@@ -68,18 +68,22 @@ __global__ void k_gamma_phase(const double* __restrict__ E, const double* __rest
 
 template <class T>
 __global__ void k_pack_k4(const double* __restrict__ dlt, int M, int NP, T* __restrict__ out) {
-  // out[((g*NRT + rt)*(NP/4) + kc)*64 + l] = Delta[g][16 rt + l%16][4 kc + l/16]
+  // lane l's 16-byte word kg of row tile rt holds Delta[g][16 rt + l%16][4 kc + l/16] for the
+  // W consecutive k chunks kc = W kg + w
+  constexpr int W = 16 / sizeof(T);
   const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t per_g = static_cast<int64_t>(NP) * NP;
   if (idx >= per_g * M) return;
   const int g = static_cast<int>(idx / per_g);
   int64_t r = idx - g * per_g;
+  const int w = static_cast<int>(r % W);
+  r /= W;
   const int l = static_cast<int>(r & 63);
   r >>= 6;
-  const int kc = static_cast<int>(r % (NP / 4));
-  const int rt = static_cast<int>(r / (NP / 4));
+  const int kg = static_cast<int>(r % (NP / 4 / W));
+  const int rt = static_cast<int>(r / (NP / 4 / W));
   const int row = 16 * rt + (l & 15);
-  const int col = 4 * kc + (l >> 4);
+  const int col = 4 * (W * kg + w) + (l >> 4);
   out[idx] = static_cast<T>(dlt[(static_cast<size_t>(g) * NP + row) * NP + col]);
 }
 
