@@ -114,6 +114,17 @@ struct StepArgs {
   int* flags;            // AQT_RUN_* flags of the context (OR-ed)
 };
 
+// The kernels read their arguments where the launch left them (kernel-argument segment or
+// the batch's argument array), as scalar loads from constant memory.  Held in registers for a
+// whole kernel, the forty-odd pointers overflow the scalar registers into vector-register
+// lanes (500 lane reads at 32 levels), so code off the step's main path takes them afresh.
+using CArgs = const __attribute__((address_space(4))) StepArgs;
+__device__ __forceinline__ CArgs& fresh(CArgs& a) {
+  CArgs* p = &a;
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+
 __device__ __forceinline__ d4 mfma_k4(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
@@ -181,16 +192,16 @@ struct Frag<ModeBF16> {
 };
 
 template <class Mode>
-__device__ __forceinline__ Frag<Mode> load_frag(const StepArgs& a, size_t idx) {
+__device__ __forceinline__ Frag<Mode> load_frag(CArgs& a, size_t idx, unsigned lane = 0) {
   Frag<Mode> f;
   if constexpr (Mode::KC == 4) {
-    f = static_cast<const Frag<Mode>*>(a.dlt_a)[idx];
+    f = (static_cast<const Frag<Mode>*>(a.dlt_a) + idx)[lane];
   } else if constexpr (Mode::KC == 16) {
-    f.h = static_cast<const uint2*>(a.dlt_a)[idx];
-    f.l = static_cast<const uint2*>(a.dlt_b)[idx];
+    f.h = (static_cast<const uint2*>(a.dlt_a) + idx)[lane];
+    f.l = (static_cast<const uint2*>(a.dlt_b) + idx)[lane];
   } else {
-    f.h = static_cast<const uint4*>(a.dlt_a)[idx];
-    f.l = static_cast<const uint4*>(a.dlt_b)[idx];
+    f.h = (static_cast<const uint4*>(a.dlt_a) + idx)[lane];
+    f.l = (static_cast<const uint4*>(a.dlt_b) + idx)[lane];
   }
   return f;
 }
@@ -402,21 +413,30 @@ struct DrawCache {
   }
 };
 
-// Per-trajectory cache of Philox blocks in LDS: blocks rngb[t] and rngb[t] + 1 of
-// trajectory t's stream, refreshed after each crossing to B = (3 m + 1) / 4 so that the
-// draws of the next jump (3m+1, 3m+2 and the threshold 3m+3) are waiting there.  The
-// refresh of the trajectories listed after a step runs on one wavefront at the start of
-// the next step, off the crossing handler's path.
+// Per-trajectory cache of Philox blocks in LDS: block x of trajectory t's stream sits in
+// slot x & 3, and blocks b[t] and b[t] + 1 are there, b[t] = (3 m + 1) / 4 after m jumps, so
+// that the draws of the next jump (3m+1, 3m+2 and the threshold 3m+3) are waiting.  One jump
+// moves b[t] on by at most one block; a wavefront without a crossing of its own computes that
+// block b[t] + 2 while the handlers run (rng_ahead).  A trajectory it could not serve (several
+// jumps in one step, or every wavefront handling a crossing) is listed and refilled by
+// wavefront 0 at the start of the next step (rng_refill).
 struct RngCache {
-  uint64_t (*w)[8];
+  uint64_t (*w)[16];
   uint64_t* b;
   int* list;
   int* n;
 };
 
+// Block x of trajectory t into its slot.
+__device__ __forceinline__ void rng_block(CArgs& a, int64_t tb, int t, uint64_t x, RngCache rc) {
+  const Philox4 r = philox4x64_10(a.traj0 + static_cast<uint64_t>(tb + t), x, 0, 0, a.seed, a.iid);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) rc.w[t][4 * (x & 3) + k] = r.w[k];
+}
+
 // Blocks B and B + 1, B = (3 m + 1) / 4, for n trajectories (list, or 0..n-1 when list
 // is null; m = 0 when m_of is null): one wavefront, two lanes per trajectory.
-__device__ void rng_refill(const StepArgs& a, int64_t tb, int n, const int* list, const int* m_of, RngCache rc,
+__device__ void rng_refill(CArgs& a, int64_t tb, int n, const int* list, const int* m_of, RngCache rc,
                            int lane) {
   for (int i0 = 0; i0 < 2 * n; i0 += kWave) {
     const int i = i0 + lane;
@@ -425,12 +445,23 @@ __device__ void rng_refill(const StepArgs& a, int64_t tb, int n, const int* list
       const int half = i & 1;
       const uint64_t mm = m_of ? static_cast<uint64_t>(m_of[t]) : 0ull;
       const uint64_t B = (3ull * mm + 1ull) >> 2;
-      const Philox4 r = philox4x64_10(a.traj0 + static_cast<uint64_t>(tb + t), B + half, 0, 0, a.seed, a.iid);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) rc.w[t][4 * half + k] = r.w[k];
+      rng_block(a, tb, t, B + half, rc);
       if (half == 0) rc.b[t] = B;
     }
   }
+}
+
+// One wavefront, lane t of the trajectories in `mask` with m jumps so far: the block that the
+// cache lacks after one more jump.  Its slot holds neither of the two blocks in use.
+__device__ __forceinline__ void rng_ahead(CArgs& a, int64_t tb, uint64_t mask, int m, RngCache rc, int lane) {
+  const uint64_t B = (3ull * static_cast<uint64_t>(m) + 1ull) >> 2, Bn = (3ull * static_cast<uint64_t>(m) + 4ull) >> 2;
+  if (((mask >> lane) & 1ull) && Bn != B) rng_block(a, tb, lane, B + 2, rc);
+}
+
+// Orders LDS accesses of the lanes of one wavefront (which executes them in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // Convergence of the crossing-time iteration: a step below tol * dt ends it.
@@ -446,13 +477,22 @@ __device__ constexpr H newton_tol() {
 // precision runs take the crossing time, the channel scans and the renormalisation
 // in FP32 (native exponentials, 32-bit shuffles).  The crossing test itself and
 // the observable sums stay in FP64 in every mode.
-template <int NP, class T, bool STAGED>
-__device__ void finish_crossing(const StepArgs& a, int g, int t, int64_t jloc, TileCols<NP, T>* S,
+// cre, cim: the trajectory's column in LDS (real and imaginary parts by level).  WAVE: the
+// one-wavefront kernel, which hands over Gamma and e^{G dt / 2} of this lane's levels in
+// registers (tw) and keeps the Philox cache filled itself (rc.b = end of the filled blocks).
+template <class T, int PL>
+struct LaneTables {
+  T G[PL], up[PL];
+};
+template <int NP, class T, bool STAGED, bool WAVE>
+__device__ void finish_crossing(CArgs& args, int g, int t, int64_t jloc, T* cre, T* cim,
                                 const double* s_r, double* s_rn, int* s_m, int* s_cnt, int* s_net, double* s_p,
-                                int* s_kind, RngCache rc, const double* tg, const float4* chs) {
+                                int* s_kind, RngCache rc, bool ahead, int gsz, const double* tg, const float4* chs,
+                                const LaneTables<T, NP / seg_width<NP>()>& tw) {
   using H = T;
   constexpr int SEG = seg_width<NP>();
   constexpr int PL = NP / SEG;
+  CArgs& a = fresh(args);
   const int lane = threadIdx.x & (SEG - 1);                    // lane within the segment
   const int base = (threadIdx.x & (kWave - 1)) & ~(SEG - 1);   // first lane of the segment
   const double dt = a.tlen[g];
@@ -469,17 +509,21 @@ __device__ void finish_crossing(const StepArgs& a, int g, int t, int64_t jloc, T
 #pragma unroll
   for (int j = 0; j < PL; ++j) {
     const int x = lane + SEG * j;
-    const bool in = x < NP;
-    G[j] = in ? static_cast<H>(Gam[x]) : H(0);
-    up[j] = in ? static_cast<H>(Eh[x]) : H(0);
-    sr[j] = in ? static_cast<H>(amp<NP, T>(S, t, 0, x)) : H(0);
-    si[j] = in ? static_cast<H>(amp<NP, T>(S, t, 1, x)) : H(0);
+    if constexpr (WAVE) {
+      G[j] = tw.G[j];
+      up[j] = tw.up[j];
+    } else {
+      G[j] = static_cast<H>(Gam[x]);
+      up[j] = static_cast<H>(Eh[x]);
+    }
+    sr[j] = cre[x];
+    si[j] = cim[x];
   }
   double r = s_r[t];
   int m = s_m[t];
+  const int m0 = m;
   int cnt = s_cnt[t];
   int net = s_net[t];
-  const int gsz = a.gs[g];
   const double tk = a.tbeg[g];
   // the crossing test of the whole step, in FP64 as in the threshold pass:
   // sum_b |c_b|^2 e^{-G_b dt} = sum |S|^2
@@ -503,18 +547,31 @@ __device__ void finish_crossing(const StepArgs& a, int g, int t, int64_t jloc, T
     }
     return;
   }
-  // draws: the two cached blocks, else Philox blocks evaluated across the segment's lanes
-  const uint64_t Bc = rc.b[t];
+  // draws of the next jump: the cached blocks; past them the segment's lanes evaluate blocks in
+  // parallel (WAVE: into the cache, which only this wavefront touches)
+  uint64_t Bc = rc.b[t];
   DrawCache<SEG> far;
   bool far_ready = false;
+  auto fill_cache = [&](int m) {
+    const uint64_t B = (3ull * static_cast<uint64_t>(m) + 1ull) >> 2;
+    if (((3ull * static_cast<uint64_t>(m) + 3ull) >> 2) < Bc) return;
+    // blocks below B are spent: slots of B .. B + 3 are free from Bc on
+    const uint64_t x = max(B, Bc) + static_cast<uint64_t>(lane);
+    if (x < B + 4) rng_block(a, jloc - t, t, x, rc);
+    wave_lds_fence();
+    Bc = B + 4;
+  };
   auto draw = [&](uint64_t d) -> double {
-    const uint64_t rel = (d >> 2) - Bc;
-    if (rel < 2) return uniform_open01(rc.w[t][4 * rel + (d & 3)]);
-    if (!far_ready) {
-      far.fill(a.seed, a.iid, traj, d, base, lane);
-      far_ready = true;
+    if constexpr (WAVE) {
+      return uniform_open01(rc.w[t][d & 15]);
+    } else {
+      if ((d >> 2) - Bc < 2) return uniform_open01(rc.w[t][d & 15]);
+      if (!far_ready) {
+        far.fill(a.seed, a.iid, traj, d, base, lane);
+        far_ready = true;
+      }
+      return far(d);
     }
-    return far(d);
   };
   // amplitudes at the start of the step's decay: undo the fused e^{-G dt / 2}
   H cr[PL], ci[PL];
@@ -591,6 +648,7 @@ __device__ void finish_crossing(const StepArgs& a, int g, int t, int64_t jloc, T
       ci[j] *= hf[j];
     }
     tau_e += static_cast<double>(tau);
+    if constexpr (WAVE) fill_cache(m);
     const H u1 = static_cast<H>(draw(3ull * m + 1));
     const H u2 = static_cast<H>(draw(3ull * m + 2));
     // source level b: first index whose running sum of q_b Gamma_b exceeds u1 * total
@@ -764,10 +822,8 @@ __device__ void finish_crossing(const StepArgs& a, int g, int t, int64_t jloc, T
     const double w2 = xr * xr + xi * xi;
     pt += w2;
     if (x < gsz) pg += w2;
-    if (x < NP) {
-      amp<NP, T>(S, t, 0, x) = static_cast<T>(cr[j]);
-      amp<NP, T>(S, t, 1, x) = static_cast<T>(ci[j]);
-    }
+    cre[x] = cr[j];
+    cim[x] = ci[j];
   }
   pg = seg_sum<SEG>(pg);
   pt = seg_sum<SEG>(pt);
@@ -777,7 +833,13 @@ __device__ void finish_crossing(const StepArgs& a, int g, int t, int64_t jloc, T
     s_m[t] = m;
     s_cnt[t] = cnt;
     s_net[t] = net;
-    if (((3ull * static_cast<uint64_t>(m) + 1ull) >> 2) != Bc) rc.list[atomicAdd(rc.n, 1)] = t;
+    if constexpr (WAVE) {
+      rc.b[t] = Bc;
+    } else {
+      const uint64_t B = (3ull * static_cast<uint64_t>(m) + 1ull) >> 2;
+      if (ahead && m == m0 + 1) rc.b[t] = B;
+      else if (B != Bc) rc.list[atomicAdd(rc.n, 1)] = t;
+    }
   }
 }
 
@@ -818,7 +880,7 @@ struct TileShared {
   double p[TT];
   int m[TT], cnt[TT], net[TT];
   int kind[3];
-  uint64_t rng[TT][8];   // Philox blocks of each trajectory's next draws (RngCache)
+  uint64_t rng[TT][16];  // Philox blocks of each trajectory's next draws (RngCache)
   uint64_t rngb[TT];
   int rfl[TT];           // trajectories whose blocks are to be refreshed
   int nrfl;
@@ -826,12 +888,12 @@ struct TileShared {
   float4 chs[stage_channels<Mode, NP>() ? kChanStage : 1];   // the step's channel entries (jump handler)
 };
 
-__device__ __forceinline__ const double* step_table(const StepArgs& a, int which) {
+__device__ __forceinline__ const double* step_table(CArgs& a, int which) {
   return which == 0 ? a.Gamma : which == 1 ? a.ehalf : which == 2 ? a.E : which == 3 ? a.d64re : a.d64im;
 }
 
 template <int NP, int TQ, class Mode, int WV>
-__device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& sh) {
+__device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& sh) {
   using T = typename Mode::T;
   using Acc = typename Mode::Acc;
   constexpr int NRT = NP / 16;
@@ -933,6 +995,8 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
 
   for (int g = 1; g < a.M_run; ++g) {
     const int gsz = a.gs[g];
+    // jumps so far of trajectory `lane`, read where no handler runs (for rng_ahead)
+    const int m_lane = (g > 1 && wave == WV - 1 && lane < TT) ? s_m[lane] : 0;
     // Philox blocks for the trajectories that jumped in the previous step (their
     // handlers listed them before the last barrier; this step's handlers read the
     // blocks only after the barrier that follows the GEMM)
@@ -1001,11 +1065,9 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
       // two wavefronts share each SIMD, and with equal priorities they issue so that one
       // finishes its share early and leaves the other to run the tail of the GEMM alone
       // (8% slower in FP32); one of each pair at a raised priority keeps both issuing to
-      // the end.  Raising waves 0-3 (wave 0 starts the step late: it refreshes the Philox
-      // caches) measured 0.6% faster than raising waves 4-7 in FP32, 0.7% in FP64 against
-      // equal priorities, and wave 0 one level higher still another 0.6% in FP32.
-      if (WV == 8 && wave == 0) __builtin_amdgcn_s_setprio(2);
-      else if (WV == 8 && wave < 4) __builtin_amdgcn_s_setprio(1);
+      // the end (waves 0-3 measured 0.6% faster than waves 4-7 in FP32, 0.7% in FP64
+      // against equal priorities).
+      if (WV == 8 && wave < 4) __builtin_amdgcn_s_setprio(1);
       for (int kg = 0; kg < NKG; kg += PF) {
 #pragma unroll
         for (int s2 = 0; s2 < PF; ++s2) {
@@ -1225,14 +1287,18 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
       constexpr int SEG = seg_width<NP>();
       constexpr int NSEG = kWave / SEG;
       const int seg = (tid & (kWave - 1)) / SEG;
+      // the last wavefront, when it has no crossing of its own, computes the Philox blocks
+      const bool ahead = ncross <= (WV - 1) * NSEG;
+      if (ahead && ncross && wave == WV - 1) rng_ahead(a, tb, cmask, m_lane, rc, lane);
       for (int e0 = wave * NSEG; e0 < ncross; e0 += WV * NSEG) {
         const int e = e0 + seg;
         if (e < ncross) {
           uint64_t mm = cmask;
           for (int k = 0; k < e; ++k) mm &= mm - 1;
           const int t = __builtin_ctzll(mm);
-          finish_crossing<NP, T, STAGED>(a, g, t, tb + t, S, s_r, s_rn, s_m, s_cnt, s_net, s_p, s_kind, rc,
-                                         &sh.tg[0][0], ch_on ? sh.chs : nullptr);
+          finish_crossing<NP, T, STAGED, false>(a, g, t, tb + t, &amp<NP, T>(S, t, 0, 0), &amp<NP, T>(S, t, 1, 0), s_r,
+                                                s_rn, s_m, s_cnt, s_net, s_p, s_kind, rc, ahead, gsz, &sh.tg[0][0],
+                                                ch_on ? sh.chs : nullptr, {});
         }
       }
     }
@@ -1283,21 +1349,418 @@ __device__ void run_tile(const StepArgs& a, int64_t tile, TileShared<NP, TQ, Mod
 #undef frag_index
 }
 
-// Wavefronts per SIMD the register allocation must leave room for: the small-level
-// FP32/BF16 kernels are latency-bound (jump handling), and three or four resident
-// wavefronts per SIMD hide more of it than the registers the compiler would
-// otherwise keep; the large-level and FP64 kernels keep the compiler's choice.
-template <int NP, class Mode>
-constexpr int min_waves_per_simd() {
-  return (sizeof(typename Mode::T) == 8 || NP > 64) ? 1 : (NP <= 16 ? 4 : 3);
+// ------------------------------------------------- one wavefront per tile ----
+// Up to kWaveLevels levels a tile belongs to one wavefront, which keeps its amplitudes in
+// the accumulators for the whole anneal and meets no barrier.  The four-wavefront tile
+// above spends its step there on latency that has nothing to hide behind: at 16 levels one
+// wavefront multiplies while three wait at three barriers, and each step waits for its own
+// table loads (4400 cycles for four MFMAs).  Here
+//   * the MFMA B operand is made from the accumulators by lane-row exchanges (none in
+//     FP64 and in the K = 16 BF16 form, whose accumulator and operand layouts agree);
+//   * Delta, the phase factors and the handler's decay tables are loaded one step ahead;
+//   * thresholds and norms sit in lanes: lane t holds trajectory t, a step without a
+//     crossing never touches LDS;
+//   * a pass over the crossings takes 64 / seg_width of them (one per segment) through a
+//     small LDS column buffer;
+//   * Philox blocks are computed for all trajectories of the tile at once, up to four
+//     blocks ahead, when a crossing finds its cache empty.
+// Microseconds a step, four wavefronts -> one: 16 levels, 1000 trajectories FP64 1.77 -> 1.15,
+// FP32 2.44 -> 0.99; 32 levels, 10^5 trajectories FP32 27.3 -> 18.5, BF16 26.9 -> 16.4, FP64
+// 71.9 -> 32.7.  At 64 levels it spills (FP32, 30000 trajectories 15.6 -> 41), so the
+// four-wavefront tile stays there.
+constexpr int kWaveLevels = 32;
+
+template <int NP, int TQ, class Mode>
+struct WaveShared {
+  using T = typename Mode::T;
+  static constexpr int TT = 8 * TQ;
+  static constexpr int NSEG = kWave / seg_width<NP>();
+  T X[NSEG][2][NP + kPad];   // columns of the crossings of a pass
+  double r[TT], p[TT];
+  uint64_t rng[TT][16], rngb[TT];
+  int m[TT], cnt[TT], net[TT];
+  int kind[3];
+};
+
+// Swap the odd 16-lane rows of x with the even rows of y (W = 16), or the upper half of x
+// with the lower half of y (W = 32).
+template <int W>
+__device__ __forceinline__ void row_swap(uint32_t& x, uint32_t& y) {
+  const auto s = (W == 16) ? __builtin_amdgcn_permlane16_swap(x, y, false, false)
+                           : __builtin_amdgcn_permlane32_swap(x, y, false, false);
+  x = s[0];
+  y = s[1];
+}
+
+// B operands of one column tile from its accumulators c[row tile] (rows 4 (lane / 16) + i,
+// FP64 lane / 16 + 4 i): B of k chunk k holds row 4 k + lane / 16.
+template <int NRT>
+__device__ __forceinline__ void wave_operand(const d4 (&c)[NRT], double (&b)[4 * NRT]) {
+#pragma unroll
+  for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[4 * rt + i] = c[rt][i];
+}
+template <int NRT>
+__device__ __forceinline__ void wave_operand(const f4 (&c)[NRT], float (&b)[4 * NRT]) {
+#pragma unroll
+  for (int rt = 0; rt < NRT; ++rt) {
+    uint32_t v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = __float_as_uint(c[rt][i]);
+    row_swap<32>(v[0], v[2]);
+    row_swap<32>(v[1], v[3]);
+    row_swap<16>(v[0], v[1]);
+    row_swap<16>(v[2], v[3]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[4 * rt + i] = __uint_as_float(v[i]);
+  }
 }
 
 template <int NP, int TQ, class Mode>
-__global__ __launch_bounds__((waves_for<NP, Mode>() * 64))
-__attribute__((amdgpu_waves_per_eu(min_waves_per_simd<NP, Mode>()))) void k_trajectories(StepArgs a) {
-  constexpr int WV = waves_for<NP, Mode>();
-  __shared__ TileShared<NP, TQ, Mode, WV> sh;
-  run_tile<NP, TQ, Mode, WV>(a, blockIdx.x, sh);
+__device__ void run_wave(CArgs& a, int64_t tile, WaveShared<NP, TQ, Mode>& sh) {
+  using T = typename Mode::T;
+  using Acc = typename Mode::Acc;
+  constexpr int NRT = NP / 16, TT = 8 * TQ, NKC = NP / Mode::KC;
+  constexpr int FW = frag_chunks<Mode>(), NKG = NKC / FW;
+  constexpr int SEG = seg_width<NP>(), NSEG = kWave / SEG, PL = NP / SEG;
+  static_assert(TT <= kWave, "one lane per trajectory");
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t tb = a.t_base + tile * TT;
+  const int lc = lane & 15;
+  const int part = (lane >> 3) & 1;
+  const bool valid = lane < TT && tb + lane < a.K;
+  const int tl = lane < TT ? lane : 0;   // this lane's trajectory in the LDS arrays
+  const RngCache rc{sh.rng, sh.rngb, nullptr, nullptr};
+
+  if (lane < TT) {
+    sh.m[lane] = 0;
+    sh.cnt[lane] = 0;
+    sh.net[lane] = 0;
+    sh.rngb[lane] = 0;
+  }
+  if (lane < 3) sh.kind[lane] = 0;
+  wave_lds_fence();
+  // Philox blocks up to four from the one of the next jump's first draw, kWave / TT at a time
+  constexpr int LPT = kWave / TT;
+  auto refill = [&]() {
+    const int t = lane / LPT;
+    const uint64_t B = (3ull * static_cast<uint64_t>(sh.m[t]) + 1ull) >> 2, end = sh.rngb[t];
+    const uint64_t x = end + static_cast<uint64_t>(lane % LPT);
+    if (x < B + 4) rng_block(a, tb, t, x, rc);
+    wave_lds_fence();
+    if (lane % LPT == 0) sh.rngb[t] = min(end + static_cast<uint64_t>(LPT), B + 4);
+    wave_lds_fence();
+  };
+  refill();
+  double r = valid ? uniform_open01(sh.rng[tl][0]) : 2.0;   // draw 0
+  if (lane < TT) sh.r[lane] = r;
+
+  // Delta fragments and tables of the next step
+  Frag<Mode> A[NRT][NKG];
+  T npre[NRT][4], npim[NRT][4];
+  double nG[PL], nup[PL];
+  // (uniform base plus a 32-bit lane offset: one offset register for all of them)
+  const unsigned ul = lane, row0 = Mode::row(lane, 0);
+  auto load_delta = [&](int g) {
+    const size_t g0 = static_cast<size_t>(g) * (NRT * NKG * kWave);
+#pragma unroll
+    for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+      for (int k = 0; k < NKG; ++k) A[rt][k] = load_frag<Mode>(a, g0 + (rt * NKG + k) * kWave, ul);
+  };
+  auto load_tables = [&](int g) {
+    const T* dr = static_cast<const T*>(a.dre) + static_cast<size_t>(g) * NP;
+    const T* di = static_cast<const T*>(a.dim) + static_cast<size_t>(g) * NP;
+#pragma unroll
+    for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        npre[rt][i] = (dr + (rt * 16 + Mode::row(0, i)))[row0];
+        npim[rt][i] = (di + (rt * 16 + Mode::row(0, i)))[row0];
+      }
+    const double* Gg = a.Gamma + static_cast<size_t>(g) * NP;
+    const double* Eg = a.ehalf + static_cast<size_t>(g) * NP;
+#pragma unroll
+    for (int j = 0; j < PL; ++j) {
+      nG[j] = (Gg + SEG * j)[ul & (SEG - 1)];
+      nup[j] = (Eg + SEG * j)[ul & (SEG - 1)];
+    }
+  };
+  const int glast = a.M_run - 1;
+  load_tables(min(1, glast));
+  load_delta(min(2, glast));
+  int gs_next = a.gs[min(1, glast)];
+
+  Acc acc[TQ][NRT];
+#pragma unroll
+  for (int q = 0; q < TQ; ++q)
+#pragma unroll
+    for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[q][rt][i] = part ? T(0) : static_cast<T>(a.cinit[rt * 16 + Mode::row(lane, i)]);
+
+  for (int g = 1; g <= glast; ++g) {
+    const int gsz = gs_next;
+    T dre[NRT][4], dim[NRT][4];
+    LaneTables<T, PL> tw;
+#pragma unroll
+    for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        dre[rt][i] = npre[rt][i];
+        dim[rt][i] = npim[rt][i];
+      }
+#pragma unroll
+    for (int j = 0; j < PL; ++j) {
+      tw.G[j] = static_cast<T>(nG[j]);
+      tw.up[j] = static_cast<T>(nup[j]);
+    }
+    const int gn = min(g + 1, glast);
+    load_tables(gn);
+    gs_next = a.gs[gn];
+    // ---- 1. C + Delta C, the k chunks of each accumulator in ascending order
+    if (g > 1) {
+#pragma unroll
+      for (int q = 0; q < TQ; ++q) {
+        if constexpr (Mode::KC == 4) {
+          T b[4 * NRT];
+          wave_operand<NRT>(acc[q], b);
+#pragma unroll
+          for (int k = 0; k < NKC; ++k)
+#pragma unroll
+            for (int rt = 0; rt < NRT; ++rt) acc[q][rt] = mfma_k4(A[rt][k / FW].v[k % FW], b[k], acc[q][rt]);
+        } else {
+          uint32_t h[NRT][2], l[NRT][2];
+#pragma unroll
+          for (int rt = 0; rt < NRT; ++rt) {
+            float x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = acc[q][rt][i];
+            s16x4 bh, bl;
+            split4(x, bh, bl);
+            const uint2 hh = __builtin_bit_cast(uint2, bh), ll = __builtin_bit_cast(uint2, bl);
+            h[rt][0] = hh.x;
+            h[rt][1] = hh.y;
+            l[rt][0] = ll.x;
+            l[rt][1] = ll.y;
+          }
+          if constexpr (Mode::KC == 16) {
+#pragma unroll
+            for (int rt = 0; rt < NRT; ++rt) {
+              const s16x4 ah = __builtin_bit_cast(s16x4, A[rt][0].h), al = __builtin_bit_cast(s16x4, A[rt][0].l);
+              const s16x4 bh = __builtin_bit_cast(s16x4, make_uint2(h[0][0], h[0][1]));
+              const s16x4 bl = __builtin_bit_cast(s16x4, make_uint2(l[0][0], l[0][1]));
+              Acc c = acc[q][rt];
+              c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, c, 0, 0, 0);
+              c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, c, 0, 0, 0);
+              c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh, c, 0, 0, 0);
+              acc[q][rt] = c;
+            }
+          } else {
+            // chunk k: lane row j holds rows 32 k + 8 j .. + 7 (two 4-row words of row tile 2k + j / 2)
+#pragma unroll
+            for (int k = 0; k < NKC; ++k) {
+#pragma unroll
+              for (int e = 0; e < 2; ++e) {
+                row_swap<32>(h[2 * k][e], h[2 * k + 1][e]);
+                row_swap<16>(h[2 * k][e], h[2 * k + 1][e]);
+                row_swap<32>(l[2 * k][e], l[2 * k + 1][e]);
+                row_swap<16>(l[2 * k][e], l[2 * k + 1][e]);
+              }
+              const bf16x8 bh = __builtin_bit_cast(bf16x8, make_uint4(h[2 * k][0], h[2 * k][1], h[2 * k + 1][0], h[2 * k + 1][1]));
+              const bf16x8 bl = __builtin_bit_cast(bf16x8, make_uint4(l[2 * k][0], l[2 * k][1], l[2 * k + 1][0], l[2 * k + 1][1]));
+#pragma unroll
+              for (int rt = 0; rt < NRT; ++rt) {
+                const bf16x8 ah = __builtin_bit_cast(bf16x8, A[rt][k].h), al = __builtin_bit_cast(bf16x8, A[rt][k].l);
+                Acc c = acc[q][rt];
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, c, 0, 0, 0);
+                acc[q][rt] = c;
+              }
+            }
+          }
+        }
+      }
+      load_delta(gn);
+    }
+    // ---- 2. C' = d o C; squared norms and ground-cluster weights in FP64, lane t's
+    // trajectory t selected from the column sums
+    double nu = 0.0, gw = 0.0;
+#pragma unroll
+    for (int q = 0; q < TQ; ++q) {
+      double nq = 0.0, gq = 0.0;
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt) {
+        double sq[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const T y = acc[q][rt][i];
+          const T yp = xor8(y);       // the other part of the same amplitude
+          const T yr = part ? yp : y, yi = part ? y : yp;
+          const T drv = dre[rt][i], div = dim[rt][i];
+          const T c = part ? (drv * yi + div * yr) : (drv * yr - div * yi);
+          acc[q][rt][i] = c;
+          const double cd = static_cast<double>(c);
+          sq[i] = cd;
+          nq = fma(cd, cd, nq);
+        }
+        if (rt * 16 < gsz) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const double v = (rt * 16 + Mode::row(lane, i) < gsz) ? sq[i] : 0.0;
+            gq = fma(v, v, gq);
+          }
+        }
+      }
+      nq += xor8(nq);
+      nq = swap_add<16>(nq);
+      nq = swap_add<32>(nq);
+      gq += xor8(gq);
+      gq = swap_add<16>(gq);
+      gq = swap_add<32>(gq);
+      if ((lane >> 3) == q) {
+        nu = nq;
+        gw = gq;
+      }
+    }
+    // ---- 3. threshold test and crossings
+    const uint64_t cmask = __ballot(valid && nu <= r);
+    double p = valid ? gw / nu : 0.0;
+    if (cmask) {
+      // two jumps of every crossing need blocks up to (3 m + 6) / 4
+      for (;;) {
+        const bool lack = ((cmask >> lane) & 1ull) &&
+                          ((3ull * static_cast<uint64_t>(sh.m[tl]) + 6ull) >> 2) >= sh.rngb[tl];
+        if (!__ballot(lack)) break;
+        refill();
+      }
+      uint64_t left = cmask;
+      while (left) {
+        // the lowest NSEG crossings; seg's own is the seg-th of them
+        uint64_t sel = 0;
+        int t = 0;
+        const int seg = lane / SEG;
+        int n = 0;
+#pragma unroll
+        for (int e = 0; e < NSEG; ++e)
+          if (left) {
+            const int te = __builtin_ctzll(left);
+            left &= left - 1;
+            sel |= 1ull << te;
+            if (seg == e) t = te;
+            ++n;
+          }
+#pragma unroll
+        for (int q = 0; q < TQ; ++q) {
+          if (!((sel >> (8 * q)) & 0xffull)) continue;
+          const int tq = 8 * q + (lane & 7);
+          if ((sel >> tq) & 1ull) {
+            T* x = &sh.X[__popcll(sel & ((1ull << tq) - 1ull))][part][0];
+#pragma unroll
+            for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) x[rt * 16 + Mode::row(lane, i)] = acc[q][rt][i];
+          }
+        }
+        wave_lds_fence();
+        if (seg < n)
+          finish_crossing<NP, T, false, true>(a, g, t, tb + t, &sh.X[seg][0][0], &sh.X[seg][1][0], sh.r, sh.r, sh.m,
+                                              sh.cnt, sh.net, sh.p, sh.kind, rc, false, gsz, nullptr, nullptr, tw);
+        wave_lds_fence();
+#pragma unroll
+        for (int q = 0; q < TQ; ++q) {
+          if (!((sel >> (8 * q)) & 0xffull)) continue;
+          const int tq = 8 * q + (lane & 7);
+          if ((sel >> tq) & 1ull) {
+            const T* x = &sh.X[__popcll(sel & ((1ull << tq) - 1ull))][part][0];
+#pragma unroll
+            for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) acc[q][rt][i] = x[rt * 16 + Mode::row(lane, i)];
+          }
+        }
+        wave_lds_fence();
+      }
+      if ((cmask >> lane) & 1ull) {
+        r = sh.r[lane];
+        p = sh.p[lane];
+      }
+    }
+    // ---- 4. per-tile observable sums
+    const double sp = seg_sum<64>(p);
+    const double sq = seg_sum<64>(p * p);
+    if (lane == 0) {
+      double* dst = a.partial + (static_cast<size_t>(a.tile0 + tile) * a.M + g) * 2;
+      *reinterpret_cast<double2*>(dst) = make_double2(sp, sq);
+    }
+  }
+  // ---- per-trajectory results
+  if (valid) {
+    const int64_t j = tb + lane;
+    if (a.jump_count) a.jump_count[j] = sh.cnt[lane];
+    if (a.net_gs) a.net_gs[j] = sh.net[lane];
+    if (a.net_hist) {
+      int v = sh.net[lane];
+      v = v < a.hist_lo ? a.hist_lo : (v > a.hist_hi ? a.hist_hi : v);
+      atomicAdd(reinterpret_cast<unsigned long long*>(&a.net_hist[v - a.hist_lo]), 1ull);
+    }
+  }
+  if (a.final_state) {
+#pragma unroll
+    for (int q = 0; q < TQ; ++q) {
+      const int64_t j = tb + 8 * q + (lane & 7);
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int x = rt * 16 + Mode::row(lane, i);
+          if (j < a.K && x < a.n) a.final_state[(j * a.n + x) * 2 + part] = static_cast<double>(acc[q][rt][i]);
+        }
+    }
+  }
+  if (a.jump_totals && lane < 3 && sh.kind[lane])
+    atomicAdd(reinterpret_cast<unsigned long long*>(&a.jump_totals[lane]),
+              static_cast<unsigned long long>(sh.kind[lane]));
+  wave_lds_fence();   // the shared state may be reused by the caller
+}
+
+// Tile body of a level count: one wavefront up to kWaveLevels levels.
+template <int NP, int TQ, class Mode, bool WAVE = (NP <= kWaveLevels)>
+struct Tile {
+  static constexpr int WV = 1;
+  using Shared = WaveShared<NP, TQ, Mode>;
+  static __device__ __forceinline__ void run(CArgs& a, int64_t tile, Shared& sh) {
+    run_wave<NP, TQ, Mode>(a, tile, sh);
+  }
+};
+template <int NP, int TQ, class Mode>
+struct Tile<NP, TQ, Mode, false> {
+  static constexpr int WV = waves_for<NP, Mode>();
+  using Shared = TileShared<NP, TQ, Mode, WV>;
+  static __device__ __forceinline__ void run(CArgs& a, int64_t tile, Shared& sh) {
+    run_tile<NP, TQ, Mode, WV>(a, tile, sh);
+  }
+};
+
+// Wavefronts per SIMD the register allocation must leave room for.  The FP32 / BF16
+// four-wavefront tile at 64 levels is bound by the latency of jump handling: three.  The
+// one-wavefront tiles and FP64 at 64 levels: two (three and four measured equal or slower
+// there, up to 31 against 20 us a step at 32 levels, 64-trajectory tiles, from spills).
+// Larger levels: the compiler's choice.
+template <int NP, class Mode>
+constexpr int min_waves_per_simd() {
+  return NP > 64 ? 1 : (NP <= kWaveLevels || sizeof(typename Mode::T) == 8) ? 2 : 3;
+}
+
+template <int NP, int TQ, class Mode>
+__global__ __launch_bounds__((Tile<NP, TQ, Mode>::WV * 64))
+__attribute__((amdgpu_waves_per_eu(min_waves_per_simd<NP, Mode>()))) void k_trajectories(StepArgs) {
+  using Body = Tile<NP, TQ, Mode>;
+  __shared__ typename Body::Shared sh;
+  Body::run(*(CArgs*)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x, sh);   // its one argument
 }
 
 // Compensated (Neumaier) running sum: s + c carries the rounding error of every addition.
@@ -1394,12 +1857,11 @@ __host__ __device__ constexpr bool batch_tq(int NP, int TQ, bool f64) {
 }
 
 template <int NP, int TQ, class Mode>
-__global__ __launch_bounds__((waves_for<NP, BatchMode<NP, Mode>>() * 64))
+__global__ __launch_bounds__((Tile<NP, TQ, BatchMode<NP, Mode>>::WV * 64))
 __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<NP, BatchMode<NP, Mode>>()))) void k_batch(
     const StepArgs* __restrict__ args, const BatchItem* __restrict__ items, int n_items, int* counter) {
-  using M = BatchMode<NP, Mode>;
-  constexpr int WV = waves_for<NP, M>();
-  __shared__ TileShared<NP, TQ, M, WV> sh;
+  using Body = Tile<NP, TQ, BatchMode<NP, Mode>>;
+  __shared__ typename Body::Shared sh;
   __shared__ int s_item;
   for (;;) {
     if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
@@ -1409,7 +1871,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<NP, BatchMode<NP, Mode>>()
     if (it >= n_items) break;
     const int inst = __builtin_amdgcn_readfirstlane(items[it].inst);
     const int tile = __builtin_amdgcn_readfirstlane(items[it].tile);
-    run_tile<NP, TQ, M, WV>(args[inst], tile, sh);
+    Body::run(*reinterpret_cast<CArgs*>(reinterpret_cast<uintptr_t>(args + inst)), tile, sh);
   }
 }
 
@@ -1425,7 +1887,7 @@ hipError_t launch_tq(int TQ, const StepArgs& a, int64_t blocks, hipStream_t st) 
   if constexpr (tq_allowed(NP, tq, f64)) {                                                    \
     if (TQ == tq) {                                                                           \
       hipLaunchKernelGGL((k_trajectories<NP, tq, Mode>), dim3(static_cast<unsigned>(blocks)), \
-                         dim3(waves_for<NP, Mode>() * 64), 0, st, a);                         \
+                         dim3(Tile<NP, tq, Mode>::WV * 64), 0, st, a);                         \
       return hipGetLastError();                                                               \
     }                                                                                         \
   }
@@ -1478,8 +1940,11 @@ int explicit_tq(int NP, int precision, int tile) {
   return tq_allowed(NP, tq, f64) ? tq : 0;
 }
 
-// Split of K trajectories over the chip.  Up to 64 levels several workgroups share a CU:
-// one launch with the widest tile that still gives every CU a workgroup.  Above, a CU holds
+// Split of K trajectories over the chip.  One-wavefront tiles: 8 trajectories while the
+// launch fits the chip at once (two wavefronts per SIMD), else 16 (32 levels FP32, us a step:
+// 16000 trajectories 4.3 with 8, 5.1 with 16, 8.1 with 32; 10^5: 24.7, 18.5, 19.4 and 19.9
+// with 64).  At 64 levels several workgroups share a CU: one launch with the widest tile
+// that still gives every CU a workgroup.  Above, a CU holds
 // one workgroup, so a launch takes rounds of one tile per CU and a round costs the step
 // time of its width whether or not the CUs are full: the run is cut into the cheapest set
 // of widths whose sum covers the column tiles that fall to each CU.  Step times in
@@ -1492,6 +1957,11 @@ TilePlan plan_tiles(int NP, int precision, int64_t K, int cus) {
   const int64_t cols = (K + 7) / 8;
   const bool f64 = precision == AQT_FP64;
   TilePlan plan;
+  if (NP <= kWaveLevels) {
+    const int w = cols <= 8 * static_cast<int64_t>(cus) ? 1 : 2;
+    plan.add(w, (cols + w - 1) / w);
+    return plan;
+  }
   if (NP <= 64) {
     int best = 1;
     for (int tq : kTQ)
@@ -1772,7 +2242,7 @@ struct LaunchGroup {
   hipStream_t st;
   template <int NP, int TQ>
   hipError_t operator()() const {
-    hipLaunchKernelGGL((k_batch<NP, TQ, Mode>), dim3(grid), dim3(waves_for<NP, BatchMode<NP, Mode>>() * 64), 0, st,
+    hipLaunchKernelGGL((k_batch<NP, TQ, Mode>), dim3(grid), dim3(Tile<NP, TQ, BatchMode<NP, Mode>>::WV * 64), 0, st,
                        dargs, items, n, counter);
     return hipGetLastError();
   }
@@ -1784,7 +2254,7 @@ struct GroupOccupancy {
   template <int NP, int TQ>
   hipError_t operator()() const {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, k_batch<NP, TQ, Mode>,
-                                                        waves_for<NP, BatchMode<NP, Mode>>() * 64, 0);
+                                                        Tile<NP, TQ, BatchMode<NP, Mode>>::WV * 64, 0);
   }
 };
 
