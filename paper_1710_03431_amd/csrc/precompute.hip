@@ -988,7 +988,15 @@ aqt_status launch_gemm(aqt_ctx* ctx, const GemmArgs& g, int batch) {
 constexpr int kHxChunk = 4096;        // x per workgroup of the block product (LDS-resident)
 constexpr int kSmallEigMax = 128;     // block size of the subspace iteration, at most
 constexpr int kMaxFilterDegree = 256;  // Chebyshev filter degree, at most
-constexpr int kMaxChains = 16;         // block slots of the lock-step chains, at most
+// Block slots of the lock-step chains, at most, and grid points per chain, at least.  A
+// chain's first point starts from a random block (about 15 iterations), the others from their
+// neighbour (2 to 3).  Up to 8192 states an iteration's time is that of the small dense
+// eigenproblems, one workgroup per slot, so many short chains cost least (12 qubits, 60
+// points: 317 ms with 7 chains of 8, 116 with 30 of 2); beyond, the block products' memory
+// traffic binds and long chains do.
+constexpr int kMaxChains = 64;
+constexpr int max_chains(int N) { return N <= 8192 ? kMaxChains : 16; }
+constexpr int chain_min_run(int N) { return N <= 8192 ? 2 : 8; }
 
 // Per-slot coefficients of one block product.
 struct HxCoef {
@@ -1543,9 +1551,9 @@ aqt_status chfsi_solve(aqt_ctx* ctx, Chfsi& c, const double* eZ, const std::vect
     cold[j] = live[j] && !c.warm[j];
     anycold = anycold || cold[j];
     // a start from the neighbouring grid point converges in a few iterations; a chain head
-    // starts from the previous head, a chain length away, where the spectrum near the cut
-    // may have rearranged, and gets the budget of a cold start twice over
-    maxit[j] = !c.warm[j] ? 150 : (c.far[j] ? 300 : 80);
+    // starts from a random block, or from a point a chain length away, where the spectrum
+    // near the cut may have rearranged
+    maxit[j] = (!c.warm[j] || c.far[j]) ? 300 : 80;
   }
   auto where = [&](int j) { return "at grid point " + std::to_string(gidx[j]); };
   AQT_HIP(ctx, hipMemsetAsync(c.status.p, 0, static_cast<size_t>(nb) * 4, st));
@@ -1715,18 +1723,18 @@ aqt_status chfsi_canon(aqt_ctx* ctx, Chfsi& c, const std::vector<int>& gidx, int
   return AQT_OK;
 }
 
-constexpr int kChainMinRun = 8;   // grid points per chain, at least
-
 // Eigenpairs and canonical vectors of grid points g0 .. g0+cnt-1 (chunk entries
 // 0 .. cnt-1 of Vout).  The run is cut into up to c.nb contiguous chains.  The
-// chain heads are solved one after another, each warm-started from the head before
-// it (the first from the last grid point solved before), then the chains advance
-// one grid point per step in lock step.
+// chain heads are solved together, from random blocks (the first from the last grid point
+// solved before, if there is one), then the chains advance one grid point per step in lock
+// step.  (Solving the heads one after another, each from the head before it, took 63 of the
+// 82 iterations of 12 qubits and 60 points, one workgroup at work in each of the small
+// eigenproblems: 525 ms against 317.)
 aqt_status chfsi_chunk(aqt_ctx* ctx, Chfsi& c, const double* eZ, const std::vector<double>& Ag,
                        const std::vector<double>& Bg, int g0, int cnt, int ncols, int n, int NP, double tol,
                        double* Vout, size_t Vstride, int* status) {
   const int nb = c.nb;
-  const int nc = std::max(1, std::min(nb, cnt / kChainMinRun));
+  const int nc = std::max(1, std::min(nb, cnt / chain_min_run(c.N)));
   std::vector<int> head(nc + 1);
   for (int j = 0; j <= nc; ++j) head[j] = g0 + static_cast<int>(static_cast<int64_t>(j) * cnt / nc);
   // grid 0 only supplies the initial state (its ground state, checked to be
@@ -1736,20 +1744,33 @@ aqt_status chfsi_chunk(aqt_ctx* ctx, Chfsi& c, const double* eZ, const std::vect
   std::vector<int> gidx(nb, -1), nconv(nb, 0);
   aqt_status s = AQT_OK;
   for (int j = 0; j < nc; ++j) {
-    if (j > 0) {
-      AQT_HIP(ctx, hipMemcpyAsync(c.at(c.X, j), c.at(c.X, j - 1), c.blk * 8, hipMemcpyDeviceToDevice, ctx->stream));
-      c.warm[j] = 1;
-      c.far[j] = 1;
-    }
-    std::fill(gidx.begin(), gidx.end(), -1);
-    std::fill(nconv.begin(), nconv.end(), 0);
+    if (j > 0) c.warm[j] = 0;
     gidx[j] = head[j];
     nconv[j] = nconv_at(head[j]);
-    if ((s = chfsi_solve(ctx, c, eZ, Ag, Bg, gidx, nconv, 1e-12)) != AQT_OK) return s;
-    // at s = 0 only the lowest levels converged: the next solve from this block starts
-    // nearly cold
-    if (head[j] == 0) c.far[j] = 1;
   }
+  s = chfsi_solve(ctx, c, eZ, Ag, Bg, gidx, nconv, 1e-12);
+  if (s == AQT_ENUMERIC) {
+    // a head that does not converge from a random block within its budget may do so from the
+    // head before it: one after another
+    if (g0 == 0) c.warm[0] = 0;
+    for (int j = 0; j < nc; ++j) {
+      if (j > 0) {
+        AQT_HIP(ctx, hipMemcpyAsync(c.at(c.X, j), c.at(c.X, j - 1), c.blk * 8, hipMemcpyDeviceToDevice, ctx->stream));
+        c.warm[j] = 1;
+        c.far[j] = 1;
+      }
+      std::fill(gidx.begin(), gidx.end(), -1);
+      std::fill(nconv.begin(), nconv.end(), 0);
+      gidx[j] = head[j];
+      nconv[j] = nconv_at(head[j]);
+      if ((s = chfsi_solve(ctx, c, eZ, Ag, Bg, gidx, nconv, 1e-12)) != AQT_OK) return s;
+      if (head[j] == 0) c.far[j] = 1;
+    }
+  }
+  if (s != AQT_OK) return s;
+  // at s = 0 only the lowest levels converged: the next solve from this block starts
+  // nearly cold
+  if (head[0] == 0) c.far[0] = 1;
   std::fill(gidx.begin(), gidx.end(), -1);
   int len = 0;
   for (int j = 0; j < nc; ++j) {
@@ -1984,7 +2005,7 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
     const size_t kk = static_cast<size_t>(KB) * KB;
     // slots (chains solved together): up to kMaxChains, within 8 GiB of workspace
     const size_t per_slot = (4 * ch.blk + static_cast<size_t>(ch.ksplit) * kk + 5 * kk + 2 * KB) * 8;
-    ch.nb = static_cast<int>(std::max<size_t>(1, std::min<size_t>(kMaxChains, (size_t(8) << 30) / per_slot)));
+    ch.nb = static_cast<int>(std::max<size_t>(1, std::min<size_t>(max_chains(N), (size_t(8) << 30) / per_slot)));
     const size_t nb = ch.nb;
     if (ch.X.reserve(nb * ch.blk * 8) || ch.Y1.reserve(nb * ch.blk * 8) || ch.Y2.reserve(nb * ch.blk * 8) ||
         ch.W.reserve(nb * ch.blk * 8) || ch.part.reserve(nb * ch.ksplit * kk * 8) || ch.S.reserve(nb * kk * 8) ||
