@@ -94,6 +94,7 @@ aqt_status aqt_create(aqt_ctx** out, int device, void* hip_stream) {
   }
   // address of this device's no-allocation buffer (a failure only disables aqt_run_noalloc)
   (void)aqt::setup_noalloc_scratch(ctx);
+  aqt::scratch_context(device, 1);
   ctx->err.clear();
   *out = ctx;
   return AQT_OK;
@@ -120,7 +121,9 @@ void aqt_destroy(aqt_ctx* ctx) {
   (void)hipSetDevice(ctx->device);
   if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
   else (void)hipDeviceSynchronize();
+  const int device = ctx->device;
   delete ctx;
+  aqt::scratch_context(device, -1);
 }
 
 const char* aqt_last_error(const aqt_ctx* ctx) { return ctx ? ctx->err.c_str() : "null context"; }

@@ -99,6 +99,39 @@ struct aqt_ctx {
 
 namespace aqt {
 
+// Workspace of one call on a context's stream, from the device's scratch cache.  The stream is
+// synchronised before the block goes back, so a cached block is idle whichever way the call
+// ends, and the next holder may use it on any stream.
+struct ScratchBuf {
+  aqt_ctx* ctx;
+  void* p = nullptr;
+  size_t bytes = 0;
+  explicit ScratchBuf(aqt_ctx* c) : ctx(c) {}
+  ScratchBuf(const ScratchBuf&) = delete;
+  ScratchBuf& operator=(const ScratchBuf&) = delete;
+  ~ScratchBuf() { release(); }
+  void release() {
+    if (p) {
+      if (hipStreamSynchronize(ctx->stream) == hipSuccess) scratch_put(ctx->device, p, bytes);
+      else (void)hipFree(p);
+    }
+    p = nullptr;
+    bytes = 0;
+  }
+  // Grows to at least `n` bytes; contents are not preserved on growth.
+  hipError_t reserve(size_t n) {
+    if (n <= bytes && p) return hipSuccess;
+    release();
+    const hipError_t e = scratch_get(ctx->device, n, &p, &bytes);
+    if (e != hipSuccess) {
+      p = nullptr;
+      bytes = 0;
+    }
+    return e;
+  }
+  template <class T> T* as() const { return static_cast<T*>(p); }
+};
+
 #define AQT_HIP(ctx, expr)                                                              \
   do {                                                                                  \
     hipError_t _e = (expr);                                                             \

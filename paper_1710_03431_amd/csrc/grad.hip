@@ -710,7 +710,7 @@ aqt_status launch_sweep(aqt_ctx* ctx, GradArgs& ga, int64_t tiles, int cus, int 
   const size_t pt = per_tile(ga.C, ga.S);
   int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(tiles, static_cast<int64_t>(budget / pt)));
   if (chunk < tiles && chunk >= cus) chunk = (chunk / cus) * cus;
-  DevBuf ws;
+  ScratchBuf ws(ctx);
   if (ws.reserve(pt * chunk) != hipSuccess) return ctx->fail(AQT_ENOMEM, "gradient workspace allocation failed");
   char* base = static_cast<char*>(ws.p);
   const size_t st = static_cast<size_t>(chunk) * NP * NC * sizeof(T);
@@ -724,7 +724,7 @@ aqt_status launch_sweep(aqt_ctx* ctx, GradArgs& ga, int64_t tiles, int cus, int 
     hipLaunchKernelGGL((k_grad<NP, TT, T>), dim3(static_cast<unsigned>(nt)), dim3(kGThreads), 0, ctx->stream, ga);
     AQT_HIP(ctx, hipGetLastError());
   }
-  AQT_HIP(ctx, hipStreamSynchronize(ctx->stream));   // the workspace is freed on return
+  AQT_HIP(ctx, hipStreamSynchronize(ctx->stream));   // the workspace goes back on return
   return AQT_OK;
 }
 
@@ -744,7 +744,7 @@ aqt_status launch_grad(aqt_ctx* ctx, const aqt_run_params* p, double* value, dou
   hipStream_t st = ctx->stream;
 
   // forward paths from the trajectory kernel, every jump recorded
-  DevBuf jc, jr, outb, stats, status;
+  ScratchBuf jc(ctx), jr(ctx), outb(ctx), stats(ctx), status(ctx);
   if (jc.reserve(K * 4) || status.reserve(4) || stats.reserve(5 * (P + 1) * 8))
     return ctx->fail(AQT_ENOMEM, "gradient allocation failed");
   int cap = 32;

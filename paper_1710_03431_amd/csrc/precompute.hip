@@ -1445,14 +1445,16 @@ struct Chfsi {
   int nq = 0, N = 0, KB = 0, ksplit = 1;
   int nb = 1;        // block slots (chains advanced together)
   size_t blk = 0;    // doubles per slot of X, Y1, Y2, W (KB * N)
-  DevBuf X, Y1, Y2, W, part, S, C, theta, res, ws, status, act, coef, info, cl;
+  ScratchBuf X, Y1, Y2, W, part, S, C, theta, res, ws, status, act, coef, info, cl;
+  explicit Chfsi(aqt_ctx* k)
+      : X(k), Y1(k), Y2(k), W(k), part(k), S(k), C(k), theta(k), res(k), ws(k), status(k), act(k), coef(k), info(k), cl(k) {}
   std::vector<double> h_theta, h_res;
   std::vector<int> h_status, h_act, h_info;
   std::vector<HxCoef> h_coef;
   std::vector<char> warm;   // per slot: X holds the Ritz block of a nearby grid point
   std::vector<char> far;    // per slot: ... of a grid point a chain length away (chain heads)
   double hub = 0.0;         // upper bound of the spectrum (Gershgorin)
-  double* at(const DevBuf& b, int j) const { return b.as<double>() + static_cast<size_t>(j) * blk; }
+  double* at(const ScratchBuf& b, int j) const { return b.as<double>() + static_cast<size_t>(j) * blk; }
 };
 
 // Control data for the next launches (host buffers are reused: wait for the copy).
@@ -1845,7 +1847,7 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
   }
   ctx->sched_A = Ag;
   ctx->sched_B = Bg;
-  DevBuf dA, dB, dh, dJ, eZ;
+  ScratchBuf dA(ctx), dB(ctx), dh(ctx), dJ(ctx), eZ(ctx);
   if (dA.reserve(M * 8) || dB.reserve(M * 8) || dh.reserve(nq * 8) || dJ.reserve(nq * nq * 8) || eZ.reserve(N * 8))
     return ctx->fail(AQT_ENOMEM, "precompute allocation failed");
   AQT_HIP(ctx, hipMemcpyAsync(dA.p, Ag.data(), M * 8, hipMemcpyHostToDevice, st));
@@ -1876,7 +1878,7 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
   // jump-channel couplings: sz of each qubit, or for correlated baths gamma_ab(w) =
   // sum_m C_m[a][b] gamma(w; omega_c,m) with C_m = F_m F_m^T the channels sum_a F_m[a][k] sz_a,
   // each with its term's cutoff (Sec. II eq. ME2-L); chan holds the F columns
-  DevBuf chw, wcv;
+  ScratchBuf chw(ctx), wcv(ctx);
   if (!ctx->chan.empty()) {
     std::vector<double> w(static_cast<size_t>(nch) * N);
     for (int k = 0; k < nch; ++k)
@@ -1890,7 +1892,7 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
   }
   // sx parts of the channel operators (general couplings): applied as row permutations
   const bool sx = !ctx->chan_x.empty();
-  DevBuf cxv;
+  ScratchBuf cxv(ctx);
   if (sx) {
     if (cxv.reserve(ctx->chan_x.size() * 8)) return ctx->fail(AQT_ENOMEM, "channel coupling allocation failed");
     AQT_HIP(ctx, hipMemcpyAsync(cxv.p, ctx->chan_x.data(), ctx->chan_x.size() * 8, hipMemcpyHostToDevice, st));
@@ -1901,7 +1903,7 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
   if (wcv.reserve(nch * 8)) return ctx->fail(AQT_ENOMEM, "channel cutoff allocation failed");
   AQT_HIP(ctx, hipMemcpyAsync(wcv.p, wch.data(), nch * 8, hipMemcpyHostToDevice, st));
   // Lamb-shift function table over every Bohr frequency (Gershgorin bound on |e|)
-  DevBuf lambS, gl, tixd;
+  ScratchBuf lambS(ctx), gl(ctx), tixd(ctx);
   LambTable ltab{nullptr, 0.0, nullptr};
   if (ctx->lamb) {
     double hsum = 0.0;
@@ -1960,7 +1962,7 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
                           + (iterative ? 0 : 2 * static_cast<size_t>(ncols) * ncols + static_cast<size_t>(ncols) * N)  // canon ws
                           + static_cast<size_t>(nch) * n * n          // z
                           + (sx ? static_cast<size_t>(nch) * n * N : 0)   // channel operators on V
-                          + 9 * static_cast<size_t>(n) * n            // polar ws
+                          + (n < N ? 9 * static_cast<size_t>(n) * n : 0)   // polar ws
                           + N                                         // Eraw
                           + (grad ? static_cast<size_t>(n) * N + 2 * static_cast<size_t>(n) * n +
                                         2 * static_cast<size_t>(nch) * n * n
@@ -1968,18 +1970,19 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
   const size_t budget = size_t(24) << 30;   // of 288 GB HBM: all grid points of a 10-qubit instance in one chunk
   int Gc = static_cast<int>(std::max<size_t>(1, std::min<size_t>(M, budget / (per_grid * 8))));
   Gc = std::max(1, std::min(Gc, 65535 / std::max(nch, 2 * nq)));   // batched products: grid z <= 65535
-  DevBuf H, Z, Vc, Vprev, cws, zws, pws, Eraw, perm, status;
+  ScratchBuf H(ctx), Z(ctx), Vc(ctx), Vprev(ctx), cws(ctx), zws(ctx), pws(ctx), Eraw(ctx), perm(ctx), status(ctx);
   if ((!iterative && (H.reserve(static_cast<size_t>(Gc) * N * N * 8) || Z.reserve(static_cast<size_t>(Gc) * N * N * 8))) ||
       Vc.reserve(static_cast<size_t>(Gc) * ncols * N * 8) || Vprev.reserve(static_cast<size_t>(ncols) * N * 8) ||
       (!iterative && cws.reserve(static_cast<size_t>(Gc) * (2 * static_cast<size_t>(ncols) * ncols + static_cast<size_t>(ncols) * N) * 8)) ||
-      zws.reserve(static_cast<size_t>(Gc) * nch * n * n * 8) || pws.reserve(static_cast<size_t>(Gc) * 9 * n * n * 8) ||
+      zws.reserve(static_cast<size_t>(Gc) * nch * n * n * 8) ||
+      (n < N && pws.reserve(static_cast<size_t>(Gc) * 9 * n * n * 8)) ||
       Eraw.reserve(static_cast<size_t>(Gc) * N * 8) || perm.reserve(static_cast<size_t>(Gc) * N * 4) ||
       status.reserve(static_cast<size_t>(Gc) * 4))
     return ctx->fail(AQT_ENOMEM, "precompute workspace allocation failed");
-  DevBuf Yc;
+  ScratchBuf Yc(ctx);
   if (sx && Yc.reserve(static_cast<size_t>(Gc) * nch * n * N * 8))
     return ctx->fail(AQT_ENOMEM, "precompute workspace allocation failed");
-  DevBuf Wx, Hd, Qz;
+  ScratchBuf Wx(ctx), Hd(ctx), Qz(ctx);
   if (grad) {
     const size_t sn = n, sN = N, snp = NP;
     if (Wx.reserve(Gc * sn * sN * 8) || Hd.reserve(Gc * 2 * sn * sn * 8) || Qz.reserve(Gc * 2 * nch * sn * sn * 8) ||
@@ -1995,7 +1998,7 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
   }
   std::vector<int> hstat(Gc);
   const size_t Vstride = static_cast<size_t>(ncols) * N;
-  Chfsi ch;
+  Chfsi ch(ctx);
   if (iterative) {
     ch.nq = nq;
     ch.N = N;

@@ -244,7 +244,7 @@ aqt_status finish_tables(aqt_ctx* ctx) {
                      ctx->Rcol.as<double>(), ctx->ehalf.as<double>(), ctx->dre.as<double>(), ctx->dim.as<double>());
   AQT_HIP(ctx, hipGetLastError());
   {
-    DevBuf mx;
+    ScratchBuf mx(ctx);
     if (mx.reserve(sizeof(double)) != hipSuccess) return ctx->fail(AQT_ENOMEM, "table allocation failed");
     hipLaunchKernelGGL(k_max_gdt, dim3(1), dim3(256), 0, ctx->stream, ctx->Gamma.as<double>(), ctx->tlen.as<double>(),
                        ctx->M, ctx->NP, mx.as<double>());
@@ -261,11 +261,9 @@ aqt_status pack_for_precision(aqt_ctx* ctx, int precision) {
   if (ctx->packed_for == precision) return AQT_OK;
   const int64_t nd = static_cast<int64_t>(ctx->M) * ctx->NP * ctx->NP;
   const int64_t nv = static_cast<int64_t>(ctx->M) * ctx->NP;
-  ctx->pk_a.release();
-  ctx->pk_b.release();
-  ctx->pk_dre.release();
-  ctx->pk_dim.release();
-  ctx->pk_ch.release();
+  // buffers of another precision or of smaller tables are kept where they are large enough
+  if (precision != AQT_BF16) ctx->pk_b.release();
+  if (precision != AQT_FP32) ctx->pk_ch.release();
   if (precision == AQT_FP64) {
     if (ctx->pk_a.reserve(nd * 8) != hipSuccess || ctx->pk_dre.reserve(nv * 8) != hipSuccess ||
         ctx->pk_dim.reserve(nv * 8) != hipSuccess)
