@@ -31,21 +31,59 @@ constexpr int kEigMaxN = 1024;
 template <int MaxN>
 struct EigSharedN {
   static constexpr int kMax = MaxN;
+  static constexpr int kSweeps = MaxN <= 256 ? 4 : 1;   // QR sweeps applied in one pass over Z
   double v[MaxN];     // Householder vector / scratch
   double w[MaxN];     // p, then w
   double d[MaxN];     // band diagonal
   double e[MaxN];     // band off-diagonal
   double beta[MaxN];  // reflection coefficients
-  double c[MaxN];     // rotation cosines of one sweep
-  double s[MaxN];     // rotation sines of one sweep
+  // before the QR sweeps: the held-back updates of the reduction (pend); during them:
+  // rotations (cosine, sine) of the sweeps of a batch, identities outside their windows
+  union {
+    double pend[4][MaxN];
+    double2 rot[kSweeps][MaxN + 2 * kSweeps];
+  };
   double red[kEigThreads / kWave];
-  int lo, hi, done, fail;
+  int lo, hi, top, ns, done, fail;
 };
-using EigShared = EigSharedN<kEigMaxN>;
+
+// Sum over the 64 lanes by the tree of wave_sum (halves first), so with its rounding, from
+// row swaps and DPP moves instead of LDS-routed shuffles: after the first steps the partial
+// sums repeat with period 16, 8, 4, 2, so a row rotation reaches the partner lane.
+template <int CTRL>
+__device__ __forceinline__ double dpp_get(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u & 0xffffffffu), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo));
+}
+template <int W>
+__device__ __forceinline__ double half_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const int lo = static_cast<int>(u & 0xffffffffu), hi = static_cast<int>(u >> 32);
+  const auto sl = (W == 16) ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false)
+                            : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto sh = (W == 16) ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false)
+                            : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  const double a = __builtin_bit_cast(double, (static_cast<uint64_t>(static_cast<uint32_t>(sh[0])) << 32) |
+                                                  static_cast<uint32_t>(sl[0]));
+  const double b = __builtin_bit_cast(double, (static_cast<uint64_t>(static_cast<uint32_t>(sh[1])) << 32) |
+                                                  static_cast<uint32_t>(sl[1]));
+  return a + b;
+}
+__device__ __forceinline__ double lane_sum(double v) {
+  v = half_add<32>(v);
+  v = half_add<16>(v);
+  v += dpp_get<0x128>(v);   // row_ror:8
+  v += dpp_get<0x124>(v);   // row_ror:4
+  v += dpp_get<0x4E>(v);    // quad_perm [2,3,0,1]
+  v += dpp_get<0xB1>(v);    // quad_perm [1,0,3,2]
+  return v;
+}
 
 __device__ __forceinline__ double block_sum(double v, double* red) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-  v = wave_sum(v);
+  v = lane_sum(v);
   __syncthreads();
   if (lane == 0) red[wave] = v;
   __syncthreads();
@@ -55,72 +93,149 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return t;
 }
 
-// Reduce symmetric A (row-major, leading dimension lda) to tridiagonal form.
-// On exit sh.d/sh.e hold the band, sh.beta the reflection coefficients and row
-// j of A, right of the diagonal, the Householder vector of step j.  Per step the
-// product with the Householder vector and the rank-2 update of the whole trailing
-// block, reading both triangles: for matrices that stay in the caches.
+// Reduce symmetric A (row-major, leading dimension lda, order at most kEigRegN) to
+// tridiagonal form.  On exit sh.d/sh.e hold the band, sh.beta the reflection coefficients and
+// row j of A, right of the diagonal, the Householder vector of step j.
+// A launch holds a thousand such matrices, far more than the L2 caches, so the passes over
+// the trailing block set the time.  Up to two rank-2 updates are held back (sh.pend): a pass
+// applies them in registers, element by element in their order, while it forms its step's
+// product, and writes the block only when two are held.  Two steps cost two reads and one
+// write of the block instead of four and two (a product pass and an update pass each), with
+// the same rounding.  With the four-sweep batches of the QR and the back transform in
+// registers, 1000 matrices of order 256 took 147 ms before and 40 now.  Rows are shared out over wavefronts, kEigRows at a time, and read whole
+// (both triangles): lane l takes the columns l + 64 t.
+constexpr int kEigRegN = 256;
+constexpr int kEigRows = 4;
 template <class Sh>
-__device__ void wg_tridiagonalize(double* A, int N, int lda, Sh& sh) {
+__device__ __forceinline__ void wg_tridiagonalize(double* A, int N, int lda, Sh& sh) {
+  constexpr int NT = (Sh::kMax < kEigRegN ? Sh::kMax : kEigRegN) / kWave;
+  constexpr int NW = kEigThreads / kWave;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid >> 6;
+  int npend = 0;   // held-back updates: A - (pv0 pw0^T + pw0 pv0^T) - (pv1 pw1^T + pw1 pv1^T)
+  const double *pv0 = sh.pend[0], *pw0 = sh.pend[1], *pv1 = sh.pend[2], *pw1 = sh.pend[3];
+  auto updated = [&](double x, double v0i, double w0i, double v1i, double w1i, int c) {
+    if (npend > 0) x -= v0i * pw0[c] + w0i * pv0[c];
+    if (npend > 1) x -= v1i * pw1[c] + w1i * pv1[c];
+    return x;
+  };
+  __syncthreads();
   for (int j = 0; j + 2 < N; ++j) {
-    const int L = N - j - 1;
-    double* row = A + static_cast<size_t>(j) * lda + j + 1;
+    const int L = N - j - 1, c0 = j + 1;
+    double* row = A + static_cast<size_t>(j) * lda;
+    const double v0j = npend > 0 ? pv0[j] : 0.0, w0j = npend > 0 ? pw0[j] : 0.0;
+    const double v1j = npend > 1 ? pv1[j] : 0.0, w1j = npend > 1 ? pw1[j] : 0.0;
+    // row j, updated (entry i of the vector is column c0 + i)
+    for (int i = tid; i < L; i += kEigThreads) sh.v[c0 + i] = updated(row[c0 + i], v0j, w0j, v1j, w1j, c0 + i);
+    if (tid == 0) sh.d[j] = updated(row[j], v0j, w0j, v1j, w1j, j);
+    __syncthreads();
     double part = 0.0;
-    for (int i = tid + 1; i < L; i += kEigThreads) part += row[i] * row[i];
+    for (int i = tid + 1; i < L; i += kEigThreads) part += sh.v[c0 + i] * sh.v[c0 + i];
     const double tail = block_sum(part, sh.red);
-    const double x0 = row[0];
-    if (tid == 0) sh.d[j] = A[static_cast<size_t>(j) * lda + j];
-    if (tail == 0.0) {
-      if (tid == 0) {
-        sh.e[j] = x0;
-        sh.beta[j] = 0.0;
-      }
-      __syncthreads();
-      continue;
-    }
+    const double x0 = sh.v[c0];
+    const bool refl = tail != 0.0;
     const double sigma = sqrt(x0 * x0 + tail);
     const double alpha = (x0 >= 0.0) ? -sigma : sigma;
     const double v0 = x0 - alpha;
-    const double beta = 2.0 / (v0 * v0 + tail);
-    for (int i = tid; i < L; i += kEigThreads) sh.v[i] = (i == 0) ? v0 : row[i];
-    __syncthreads();
-    // p = beta * S v, S the trailing block; one wavefront per row
-    for (int i = wave; i < L; i += kEigThreads / kWave) {
-      const double* Si = A + static_cast<size_t>(j + 1 + i) * lda + j + 1;
-      double acc = 0.0;
-      for (int k = lane; k < L; k += kWave) acc += Si[k] * sh.v[k];
-      acc = wave_sum(acc);
-      if (lane == 0) sh.w[i] = beta * acc;
-    }
-    __syncthreads();
-    part = 0.0;
-    for (int i = tid; i < L; i += kEigThreads) part += sh.v[i] * sh.w[i];
-    const double Kc = 0.5 * beta * block_sum(part, sh.red);
-    for (int i = tid; i < L; i += kEigThreads) sh.w[i] -= Kc * sh.v[i];
-    __syncthreads();
-    const size_t tot = static_cast<size_t>(L) * L;
-    for (size_t f = tid; f < tot; f += kEigThreads) {
-      const int i = static_cast<int>(f / L), k = static_cast<int>(f - static_cast<size_t>(i) * L);
-      A[static_cast<size_t>(j + 1 + i) * lda + j + 1 + k] -= sh.v[i] * sh.w[k] + sh.w[i] * sh.v[k];
-    }
-    for (int i = tid; i < L; i += kEigThreads) row[i] = sh.v[i];
+    const double beta = refl ? 2.0 / (v0 * v0 + tail) : 0.0;
+    __syncthreads();   // every thread has read x0
     if (tid == 0) {
-      sh.e[j] = alpha;
+      sh.e[j] = refl ? alpha : x0;
       sh.beta[j] = beta;
+      if (refl) sh.v[c0] = v0;
+    }
+    __syncthreads();
+    for (int i = tid; i < L; i += kEigThreads) row[c0 + i] = sh.v[c0 + i];
+    const bool flush = npend == 2;
+    if (!flush && !refl) {
+      __syncthreads();   // sh.v is rewritten by other threads in the next step
+      continue;
+    }
+    double vk[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = lane + kWave * t;
+      vk[t] = (refl && c >= c0 && c < N) ? sh.v[c] : 0.0;
+    }
+    // one pass over the trailing block: p = beta S v, one wavefront per row
+    for (int i0 = c0 + kEigRows * wave; i0 < N; i0 += kEigRows * NW) {
+      double x[kEigRows][NT];
+#pragma unroll
+      for (int r = 0; r < kEigRows; ++r) {
+        const int i = min(i0 + r, N - 1);
+        const double* Si = A + static_cast<size_t>(i) * lda;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int c = lane + kWave * t;
+          x[r][t] = (c >= c0 && c < N) ? Si[c] : 0.0;
+        }
+      }
+      if (npend > 0) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int c = lane + kWave * t;
+          if (c < c0 || c >= N) continue;
+          const double a0 = pw0[c], b0 = pv0[c];
+          const double a1 = npend > 1 ? pw1[c] : 0.0, b1 = npend > 1 ? pv1[c] : 0.0;
+#pragma unroll
+          for (int r = 0; r < kEigRows; ++r) {
+            const int i = min(i0 + r, N - 1);
+            double y = x[r][t];
+            y -= pv0[i] * a0 + pw0[i] * b0;
+            if (npend > 1) y -= pv1[i] * a1 + pw1[i] * b1;
+            x[r][t] = y;
+            if (flush && i0 + r < N) A[static_cast<size_t>(i) * lda + c] = y;
+          }
+        }
+      }
+      if (refl) {
+        double acc[kEigRows];
+#pragma unroll
+        for (int r = 0; r < kEigRows; ++r) {
+          acc[r] = 0.0;
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[r] += x[r][t] * vk[t];
+        }
+#pragma unroll
+        for (int r = 0; r < kEigRows; ++r) acc[r] = lane_sum(acc[r]);
+#pragma unroll
+        for (int r = 0; r < kEigRows; ++r)
+          if (lane == 0 && i0 + r < N) sh.w[i0 + r] = beta * acc[r];
+      }
+    }
+    __syncthreads();
+    if (refl) {
+      part = 0.0;
+      for (int i = tid; i < L; i += kEigThreads) part += sh.v[c0 + i] * sh.w[c0 + i];
+      const double Kc = 0.5 * beta * block_sum(part, sh.red);
+      const int slot = flush ? 0 : npend;
+      for (int i = c0 + tid; i < N; i += kEigThreads) {
+        sh.pend[2 * slot][i] = sh.v[i];
+        double wi = sh.w[i];
+        wi -= Kc * sh.v[i];
+        sh.pend[2 * slot + 1][i] = wi;
+      }
+      npend = slot + 1;
+    } else {
+      npend = 0;   // flushed
     }
     __syncthreads();
   }
   if (tid == 0) {
     if (N >= 2) {
-      sh.d[N - 2] = A[static_cast<size_t>(N - 2) * lda + N - 2];
-      sh.e[N - 2] = A[static_cast<size_t>(N - 2) * lda + N - 1];
-      sh.beta[N - 2] = 0.0;
+      const int a = N - 2;
+      const double v0a = npend > 0 ? pv0[a] : 0.0, w0a = npend > 0 ? pw0[a] : 0.0;
+      const double v1a = npend > 1 ? pv1[a] : 0.0, w1a = npend > 1 ? pw1[a] : 0.0;
+      sh.d[a] = updated(A[static_cast<size_t>(a) * lda + a], v0a, w0a, v1a, w1a, a);
+      sh.e[a] = updated(A[static_cast<size_t>(a) * lda + a + 1], v0a, w0a, v1a, w1a, a + 1);
+      sh.beta[a] = 0.0;
     }
-    sh.d[N - 1] = A[static_cast<size_t>(N - 1) * lda + N - 1];
-    sh.e[N - 1] = 0.0;
-    sh.beta[N - 1] = 0.0;
+    const int a = N - 1;
+    const double v0a = npend > 0 ? pv0[a] : 0.0, w0a = npend > 0 ? pw0[a] : 0.0;
+    const double v1a = npend > 1 ? pv1[a] : 0.0, w1a = npend > 1 ? pw1[a] : 0.0;
+    sh.d[a] = updated(A[static_cast<size_t>(a) * lda + a], v0a, w0a, v1a, w1a, a);
+    sh.e[a] = 0.0;
+    sh.beta[a] = 0.0;
   }
   __syncthreads();
 }
@@ -128,8 +243,7 @@ __device__ void wg_tridiagonalize(double* A, int N, int lda, Sh& sh) {
 // wg_tridiagonalize for a matrix too large for the caches, where the reduction is
 // bound by HBM bandwidth (same results on exit; the rest of A is overwritten).
 // Only the lower triangle is read.  The rank-2 updates (v w^T + w v^T) are held back
-// -- up to two, in sh.c / sh.s (free until the QR sweep) and in pend (2 MaxN
-// doubles) -- and written into A every other step, in the pass that forms that
+// -- up to two, in sh.pend -- and written into A every other step, in the pass that forms that
 // step's symmetric product from the updated entries; the steps between read the
 // stale lower triangle and correct the product by the held-back updates (two dot
 // products each).  The product: row sums by wavefront reductions, the transposed
@@ -138,16 +252,16 @@ __device__ void wg_tridiagonalize(double* A, int N, int lda, Sh& sh) {
 // of the traffic of wg_tridiagonalize (which reads the full matrix for the product
 // and reads and writes it for the update, every step).
 template <class Sh>
-__device__ void wg_tridiagonalize_streamed(double* A, int N, int lda, Sh& sh, double* pend) {
+__device__ __forceinline__ void wg_tridiagonalize_streamed(double* A, int N, int lda, Sh& sh) {
   constexpr int NT = (Sh::kMax + kWave - 1) / kWave;   // column slots per lane
   constexpr int NW = kEigThreads / kWave;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1), wave = tid >> 6;
   // held-back updates r = 0, 1: the trailing block is A - sum_r (pv_r pw_r^T + pw_r pv_r^T)
-  double* pv0 = sh.c;
-  double* pw0 = sh.s;
-  double* pv1 = pend;
-  double* pw1 = pend + Sh::kMax;
+  double* pv0 = sh.pend[0];
+  double* pw0 = sh.pend[1];
+  double* pv1 = sh.pend[2];
+  double* pw1 = sh.pend[3];
   for (int i = tid; i < N; i += kEigThreads) {
     pv0[i] = 0.0;
     pw0[i] = 0.0;
@@ -302,8 +416,12 @@ __device__ void wg_tridiagonalize_streamed(double* A, int N, int lda, Sh& sh, do
 // unless from_z is set (then Z's columns are rotated as given: starting from the
 // reflection product, Z ends up holding the eigenvectors of the full matrix).
 // Returns false if the iteration budget is exhausted.
+// The rotations of a sweep depend on the band alone, so wavefront 0 computes those of up to
+// kSweeps sweeps and one pass over Z applies them all: rotation k of sweep s right after
+// rotation k + 1 of sweep s - 1, which is the order of one sweep after another for every
+// element, with the columns in flight in registers.  Z crosses memory once per batch.
 template <class Sh>
-__device__ bool wg_band_qr(double* Z, int N, int ldz, Sh& sh, bool from_z = false) {
+__device__ __forceinline__ bool wg_band_qr(double* Z, int N, int ldz, Sh& sh, bool from_z = false) {
   const int tid = threadIdx.x;
   if (!from_z)
     for (int c = 0; c < N; ++c)
@@ -315,116 +433,146 @@ __device__ bool wg_band_qr(double* Z, int N, int ldz, Sh& sh, bool from_z = fals
   }
   __syncthreads();
   const long budget = 64L * N + 64;
-  for (long sweep = 0;; ++sweep) {
+  constexpr int S = Sh::kSweeps;
+  long sweep = 0;
+  for (;;) {
     if (tid < kWave) {
-      // wavefront 0: deflation.  Negligible off-diagonal entries below hi are zeroed;
-      // the window [l, m] is the unreduced block that ends at the highest nonzero e.
-      const int m0 = sh.hi;
-      for (int k = tid; k < m0; k += kWave)
-        if (fabs(sh.e[k]) <= 2.220446049250313e-16 * (fabs(sh.d[k]) + fabs(sh.d[k + 1]))) sh.e[k] = 0.0;
-      int m = 0;
-      for (int c = (m0 - 1) / kWave; c >= 0 && m0 > 0; --c) {
-        const int k = c * kWave + tid;
-        const unsigned long long nz = __ballot(k < m0 && sh.e[k] != 0.0);
-        if (nz) {
-          m = c * kWave + (63 - __clzll(nz)) + 1;
-          break;
-        }
-      }
-      int l = 0;
-      for (int c = (m - 2) / kWave; c >= 0 && m >= 2; --c) {
-        const int k = c * kWave + tid;
-        const unsigned long long zr = __ballot(k < m - 1 && sh.e[k] == 0.0);
-        if (zr) {
-          l = c * kWave + (63 - __clzll(zr)) + 1;
-          break;
-        }
-      }
-      const bool have = m > 0;
-      if (tid == 0) {
-        sh.hi = m;
-        if (!have || sweep >= budget) {
-          sh.done = 1;
-          sh.fail = have ? 1 : 0;
-        } else {
-          // Wilkinson shift from the trailing 2x2 block of the window [l, m]
-          const double delta = 0.5 * (sh.d[m - 1] - sh.d[m]);
-          const double bb = sh.e[m - 1];
-          const double den = delta + copysign(hypot(delta, bb), delta >= 0.0 ? 1.0 : -1.0);
-          const double mu = sh.d[m] - bb * bb / den;
-          // bulge chase; the running diagonal (dk), the scaled off-diagonal (bk) and the
-          // untouched next diagonal (dn) stay in registers, the next band entries are
-          // loaded one rotation ahead.  1/r by Newton's iteration for the reciprocal
-          // square root (two steps from the hardware estimate), squares in range.
-          double x = sh.d[l] - mu, z = sh.e[l];
-          double dk = sh.d[l], bk = sh.e[l], dn = sh.d[l + 1];
-          double ek = 0.0;
-          for (int k = l; k < m; ++k) {
-            const bool more = k + 1 < m;
-            const double en = more ? sh.e[k + 1] : 0.0;
-            const double dnn = more ? sh.d[k + 2] : 0.0;
-            const double q = fma(x, x, z * z);
-            double r, ri;
-            if (q > 1e-300 && q < 1e300) {
-              double y = __builtin_amdgcn_rsq(q);
-              const double hq = 0.5 * q;
-              y = y * fma(-hq * y, y, 1.5);
-              y = y * fma(-hq * y, y, 1.5);
-              ri = y;
-              r = q * y;
-            } else {
-              r = hypot(x, z);
-              ri = 1.0 / r;
-            }
-            const double c = x * ri, s = z * ri;
-            if (k > l) sh.e[k - 1] = r;
-            const double a = dk, b = bk, cc = dn;
-            sh.d[k] = c * c * a + 2.0 * c * s * b + s * s * cc;
-            dk = s * s * a - 2.0 * c * s * b + c * c * cc;
-            ek = c * s * (cc - a) + (c * c - s * s) * b;
-            if (more) {
-              z = s * en;
-              bk = c * en;
-              dn = dnn;
-            }
-            x = ek;
-            sh.c[k] = c;
-            sh.s[k] = s;
+      int ns = 0, lo = N, top = 0;
+      bool done = false;
+      for (int bt = 0; bt < S && !done; ++bt, ++sweep) {
+        for (int k = tid; k < N + 2 * S; k += kWave) sh.rot[bt][k] = make_double2(1.0, 0.0);
+        // wavefront 0: deflation.  Negligible off-diagonal entries below hi are zeroed;
+        // the window [l, m] is the unreduced block that ends at the highest nonzero e.
+        const int m0 = sh.hi;
+        for (int k = tid; k < m0; k += kWave)
+          if (fabs(sh.e[k]) <= 2.220446049250313e-16 * (fabs(sh.d[k]) + fabs(sh.d[k + 1]))) sh.e[k] = 0.0;
+        int m = 0;
+        for (int c = (m0 - 1) / kWave; c >= 0 && m0 > 0; --c) {
+          const int k = c * kWave + tid;
+          const unsigned long long nz = __ballot(k < m0 && sh.e[k] != 0.0);
+          if (nz) {
+            m = c * kWave + (63 - __clzll(nz)) + 1;
+            break;
           }
-          sh.d[m] = dk;
-          sh.e[m - 1] = ek;
-          sh.lo = l;
+        }
+        int l = 0;
+        for (int c = (m - 2) / kWave; c >= 0 && m >= 2; --c) {
+          const int k = c * kWave + tid;
+          const unsigned long long zr = __ballot(k < m - 1 && sh.e[k] == 0.0);
+          if (zr) {
+            l = c * kWave + (63 - __clzll(zr)) + 1;
+            break;
+          }
+        }
+        const bool have = m > 0;
+        if (tid == 0) {
+          sh.hi = m;
+          if (have && sweep < budget) {
+            // Wilkinson shift from the trailing 2x2 block of the window [l, m]
+            const double delta = 0.5 * (sh.d[m - 1] - sh.d[m]);
+            const double bb = sh.e[m - 1];
+            const double den = delta + copysign(hypot(delta, bb), delta >= 0.0 ? 1.0 : -1.0);
+            const double mu = sh.d[m] - bb * bb / den;
+            // bulge chase; the running diagonal (dk), the scaled off-diagonal (bk) and the
+            // untouched next diagonal (dn) stay in registers, the next band entries are
+            // loaded one rotation ahead.  1/r by Newton's iteration for the reciprocal
+            // square root (two steps from the hardware estimate), squares in range.
+            double x = sh.d[l] - mu, z = sh.e[l];
+            double dk = sh.d[l], bk = sh.e[l], dn = sh.d[l + 1];
+            double ek = 0.0;
+            for (int k = l; k < m; ++k) {
+              const bool more = k + 1 < m;
+              const double en = more ? sh.e[k + 1] : 0.0;
+              const double dnn = more ? sh.d[k + 2] : 0.0;
+              const double q = fma(x, x, z * z);
+              double r, ri;
+              if (q > 1e-300 && q < 1e300) {
+                double y = __builtin_amdgcn_rsq(q);
+                const double hq = 0.5 * q;
+                y = y * fma(-hq * y, y, 1.5);
+                y = y * fma(-hq * y, y, 1.5);
+                ri = y;
+                r = q * y;
+              } else {
+                r = hypot(x, z);
+                ri = 1.0 / r;
+              }
+              const double c = x * ri, s = z * ri;
+              if (k > l) sh.e[k - 1] = r;
+              const double a = dk, b = bk, cc = dn;
+              sh.d[k] = c * c * a + 2.0 * c * s * b + s * s * cc;
+              dk = s * s * a - 2.0 * c * s * b + c * c * cc;
+              ek = c * s * (cc - a) + (c * c - s * s) * b;
+              if (more) {
+                z = s * en;
+                bk = c * en;
+                dn = dnn;
+              }
+              x = ek;
+              sh.rot[bt][k + S] = make_double2(c, s);
+            }
+            sh.d[m] = dk;
+            sh.e[m - 1] = ek;
+        }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (!have || sweep >= budget) {
+          done = true;
+          if (tid == 0) sh.fail = have ? 1 : 0;
+        } else {
+          ns = bt + 1;
+          lo = min(lo, l);
+          top = max(top, m);
+        }
+      }
+      if (tid == 0) {
+        sh.done = done ? 1 : 0;
+        sh.ns = ns;
+        sh.lo = lo;
+        sh.top = top;
+      }
+    }
+    __syncthreads();
+    const int ns = sh.ns, lo = sh.lo, top = sh.top;
+    if (ns > 0) {
+      for (int r = tid; r < N; r += kEigThreads) {
+        // step p: column p + 1 comes in, rotation p - b of sweep b for every b, column
+        // p + 1 - S is finished (w[i] holds column p + 1 - S + i)
+        double w[S + 1];
+#pragma unroll
+        for (int i = 0; i < S; ++i) w[i] = 0.0;
+        w[S] = Z[static_cast<size_t>(lo) * ldz + r];
+        constexpr int U = 8;   // columns loaded ahead
+        for (int p0 = lo; p0 < top + S; p0 += U) {
+          double zn[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) zn[u] = (p0 + u + 1 <= top) ? Z[static_cast<size_t>(p0 + u + 1) * ldz + r] : 0.0;
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int p = p0 + u;
+            if (p >= top + S) break;
+#pragma unroll
+            for (int i = 0; i < S; ++i) w[i] = w[i + 1];
+            w[S] = zn[u];
+#pragma unroll
+            for (int b = 0; b < S; ++b) {
+              if (b < ns) {
+                const double2 cs = sh.rot[b][p - b + S];
+                const double c = cs.x, s = cs.y;
+                const double zk = w[S - 1 - b], z1 = w[S - b];
+                w[S - 1 - b] = c * zk + s * z1;
+                w[S - b] = -s * zk + c * z1;
+              }
+            }
+            const int col = p + 1 - S;
+            if (col >= lo) Z[static_cast<size_t>(col) * ldz + r] = w[0];
+          }
         }
       }
     }
     __syncthreads();
     if (sh.done) break;
-    const int l = sh.lo, m = sh.hi;
-    for (int r = tid; r < N; r += kEigThreads) {
-      double zk = Z[static_cast<size_t>(l) * ldz + r];
-      int k = l;
-      // eight columns loaded ahead of their rotations: each column is read before the
-      // rotation that rewrites it, and the loads are in flight together
-      for (; k + 8 <= m; k += 8) {
-        double z1[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) z1[u] = Z[static_cast<size_t>(k + 1 + u) * ldz + r];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const double c = sh.c[k + u], s = sh.s[k + u];
-          Z[static_cast<size_t>(k + u) * ldz + r] = c * zk + s * z1[u];
-          zk = -s * zk + c * z1[u];
-        }
-      }
-      for (; k < m; ++k) {
-        const double zk1 = Z[static_cast<size_t>(k + 1) * ldz + r];
-        const double c = sh.c[k], s = sh.s[k];
-        Z[static_cast<size_t>(k) * ldz + r] = c * zk + s * zk1;
-        zk = -s * zk + c * zk1;
-      }
-      Z[static_cast<size_t>(m) * ldz + r] = zk;
-    }
-    __syncthreads();
   }
   const bool ok = !sh.fail;
   __syncthreads();
@@ -432,47 +580,15 @@ __device__ bool wg_band_qr(double* Z, int N, int ldz, Sh& sh, bool from_z = fals
 }
 
 // Apply the stored reflections to the columns of Z listed in cols[0..ncols-1]
-// (column-major), turning band eigenvectors into eigenvectors of A.  Per
-// reflection one pass for the dot products with the columns and one for their
-// update: for matrices that stay in the caches.
-template <class Sh>
-__device__ void wg_back_transform(const double* A, int N, int lda, double* Z, int ldz, const int* cols, int ncols,
-                                  Sh& sh) {
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = tid >> 6;
-  for (int j = N - 3; j >= 0; --j) {
-    const double beta = sh.beta[j];
-    if (beta == 0.0) continue;
-    const int L = N - j - 1;
-    const double* vrow = A + static_cast<size_t>(j) * lda + j + 1;
-    for (int i = tid; i < L; i += kEigThreads) sh.v[i] = vrow[i];
-    __syncthreads();
-    for (int q = wave; q < ncols; q += kEigThreads / kWave) {
-      const double* zc = Z + static_cast<size_t>(cols[q]) * ldz + j + 1;
-      double acc = 0.0;
-      for (int i = lane; i < L; i += kWave) acc += sh.v[i] * zc[i];
-      acc = wave_sum(acc);
-      if (lane == 0) sh.w[q] = beta * acc;
-    }
-    __syncthreads();
-    const size_t tot = static_cast<size_t>(ncols) * L;
-    for (size_t f = tid; f < tot; f += kEigThreads) {
-      const int q = static_cast<int>(f / L), i = static_cast<int>(f - static_cast<size_t>(q) * L);
-      Z[static_cast<size_t>(cols[q]) * ldz + j + 1 + i] -= sh.w[q] * sh.v[i];
-    }
-    __syncthreads();
-  }
-}
-
-// wg_back_transform for matrices too large for the caches: each wavefront holds a
+// (column-major), turning band eigenvectors into eigenvectors of A.  Each wavefront holds a
 // group of kBtCols columns of Z in registers (row lane + 64 t in slot t) while every
 // reflection is applied to them, so Z is read and written once and each reflection
-// is read once per group (wg_back_transform moves Z three times per reflection).
-constexpr int kBtCols = 2;
+// is read once per group (a pass over Z per reflection moves it three times each).
 template <class Sh>
-__device__ void wg_back_transform_streamed(const double* A, int N, int lda, double* Z, int ldz, const int* cols,
-                                           int ncols, Sh& sh) {
+__device__ __forceinline__ void wg_back_transform(const double* A, int N, int lda, double* Z, int ldz, const int* cols,
+                                  int ncols, Sh& sh) {
   constexpr int NT = (Sh::kMax + kWave - 1) / kWave;
+    constexpr int kBtCols = NT <= 4 ? 8 : 2;
   constexpr int NW = kEigThreads / kWave;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
   const int ngrp = (ncols + kBtCols - 1) / kBtCols;
@@ -508,7 +624,7 @@ __device__ void wg_back_transform_streamed(const double* A, int N, int lda, doub
         dot[c] = acc;
       }
 #pragma unroll
-      for (int c = 0; c < kBtCols; ++c) dot[c] = beta * wave_sum(dot[c]);
+      for (int c = 0; c < kBtCols; ++c) dot[c] = beta * lane_sum(dot[c]);
 #pragma unroll
       for (int c = 0; c < kBtCols; ++c)
 #pragma unroll
@@ -529,7 +645,7 @@ __device__ void wg_back_transform_streamed(const double* A, int N, int lda, doub
 // +infinity (ties by index), so perm is a permutation for any input and every
 // index read through it stays in range.
 __device__ __forceinline__ double rank_key(double v) { return (v == v) ? v : __builtin_huge_val(); }
-__device__ void wg_rank_ascending(const double* d, int N, int* perm) {
+__device__ __forceinline__ void wg_rank_ascending(const double* d, int N, int* perm) {
   for (int i = threadIdx.x; i < N; i += kEigThreads) {
     const double di = rank_key(d[i]);
     int rank = 0;

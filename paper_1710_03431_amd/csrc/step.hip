@@ -223,9 +223,13 @@ constexpr int prefetch_depth() {
 // ----------------------------------------------------------- jump handler --
 // Tile layout in LDS: S[q][c][row] holds column tile q (8 trajectories) column-
 // major; column c = (t & 7) + 8 * part carries the real (part 0) or imaginary
-// (part 1) part of local trajectory t = 8 q + (c & 7).  Columns are padded to
-// NP + kPad elements so the 16 columns of an MFMA operand fall in distinct banks.
-constexpr int kPad = 4;   // >= 4: the B read-ahead touches padding rows NP..NP+3
+// (part 1) part of local trajectory t = 8 q + (c & 7).  Columns are padded so that an MFMA
+// operand read (row 4 k + lane / 16 of column lane % 16) meets distinct banks: 4 floats, and 2
+// doubles, which are read half a wavefront at a time (4 doubles: two-way conflicts).
+template <class T>
+constexpr int col_pad() {
+  return sizeof(T) == 8 ? 2 : 4;
+}
 constexpr int kStepTables = 5;
 // Wavefronts per workgroup.  Eight (two per SIMD) let one wave's LDS and load waits
 // hide behind the other's MFMAs where each wave still has a large share of the
@@ -236,7 +240,7 @@ constexpr int waves_for() {
   return (NP >= 128 && Mode::KC == 4) ? 8 : 4;
 }
 template <int NP, class T>
-using TileCols = T[16][NP + kPad];
+using TileCols = T[16][NP + col_pad<T>()];
 
 template <int NP, class T>
 __device__ __forceinline__ T& amp(TileCols<NP, T>* S, int t, int part, int row) {
@@ -1084,14 +1088,14 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
             if (ok_u[u]) ring[s2][u] = load_frag<Mode>(a, frag_index(gn, u, kk));
           if constexpr (Mode::KC == 4 && kSharedQ) {
             // B for this chunk was read one chunk ahead; read the next one now (on
-            // the last chunk that is padding row NP + lane / 16: in bounds, unused)
+            // the last chunk that is chunk 0 again: unused)
 #pragma unroll
             for (int w = 0; w < FW; ++w) {
               const int k = (kg + s2) * FW + w;
               T bcur[QG];
 #pragma unroll
               for (int qq = 0; qq < QG; ++qq) bcur[qq] = bnx[qq];
-              const int krn = 4 * (k + 1) + (lane >> 4);
+              const int krn = (4 * (k + 1) & (NP - 1)) + (lane >> 4);
 #pragma unroll
               for (int qq = 0; qq < QG; ++qq) bnx[qq] = S[qq][lc][krn];
 #pragma unroll
@@ -1375,7 +1379,7 @@ struct WaveShared {
   using T = typename Mode::T;
   static constexpr int TT = 8 * TQ;
   static constexpr int NSEG = kWave / seg_width<NP>();
-  T X[NSEG][2][NP + kPad];   // columns of the crossings of a pass
+  T X[NSEG][2][NP + col_pad<T>()];   // columns of the crossings of a pass
   double r[TT], p[TT];
   uint64_t rng[TT][16], rngb[TT];
   int m[TT], cnt[TT], net[TT];

@@ -12,6 +12,7 @@
 //   fragments when only 16 levels are kept).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 
@@ -21,36 +22,56 @@
 namespace aqt {
 namespace {
 
-__global__ void k_gamma_phase(const double* __restrict__ E, const double* __restrict__ shift,
-                              const double* __restrict__ R, int M, int NP, int n,
-                              int nq, const double* __restrict__ tlen, double* __restrict__ Gamma,
-                              double* __restrict__ Rcol,
-                              double* __restrict__ ehalf, double* __restrict__ dre, double* __restrict__ dim) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= static_cast<int64_t>(M) * NP) return;
-  const int g = static_cast<int>(idx / NP);
-  const int b = static_cast<int>(idx - static_cast<int64_t>(g) * NP);
-  const double dt = tlen[g];   // length of the step into grid g
+// One workgroup per grid point (blockIdx.y) and 64 source levels b: the rows of four channels
+// are staged in LDS 16 targets at a time, so that R is read along its rows, and each thread
+// adds one row in ascending order.  (A thread per row, reading along columns, took 3.6 ms for
+// 1000 points of 256 levels and 8 channels, this 1.5; R is 4.2 GB.)
+constexpr int kGpA = 16, kGpC = 4;
+__global__ __launch_bounds__(256) void k_gamma_phase(const double* __restrict__ E, const double* __restrict__ shift,
+                                                     const double* __restrict__ R, int NP, int n, int nq,
+                                                     const double* __restrict__ tlen, double* __restrict__ Gamma,
+                                                     double* __restrict__ Rcol, double* __restrict__ ehalf,
+                                                     double* __restrict__ dre, double* __restrict__ dim) {
+  __shared__ double s_row[kGpC][64][kGpA + 1];
+  __shared__ double s_sum[kGpC][64];
+  const int g = blockIdx.y, b0 = blockIdx.x * 64, tid = threadIdx.x;
+  const int bl = tid & 63, q = tid >> 6, b = b0 + bl;
   double G = 0.0;
-  for (int i = 0; i < nq; ++i) {
+  for (int i0 = 0; i0 < nq; i0 += kGpC) {
+    const int i = i0 + q;
     double rs = 0.0, lo = 0.0, dg = 0.0;
-    if (b < n) {
-      const double* row = R + ((static_cast<size_t>(g) * nq + i) * NP + b) * NP;
-      for (int a = 0; a < n; ++a) {
-        if (a == b) {
-          lo = rs;
-          dg = row[a];
-        }
-        rs += row[a];
+    for (int a0 = 0; a0 < n; a0 += kGpA) {
+      for (int f = tid; f < kGpC * 64 * kGpA; f += 256) {
+        const int a = f % kGpA, r = (f / kGpA) % 64, c = f / (kGpA * 64);
+        s_row[c][r][a] = (i0 + c < nq && b0 + r < n && a0 + a < n)
+                             ? R[((static_cast<size_t>(g) * nq + i0 + c) * NP + b0 + r) * NP + a0 + a]
+                             : 0.0;
       }
+      __syncthreads();
+      const int na = min(kGpA, n - a0);
+      for (int a = 0; a < na; ++a) {
+        const double v = s_row[q][bl][a];
+        if (a0 + a == b) {
+          lo = rs;
+          dg = v;
+        }
+        rs += v;
+      }
+      __syncthreads();
     }
-    double* out = Rcol + ((static_cast<size_t>(g) * nq + i) * NP + b) * 4;
-    out[0] = rs;
-    out[1] = lo;
-    out[2] = dg;
-    out[3] = 0.0;
-    G += rs;
+    if (i < nq && b < NP) {
+      double* out = Rcol + ((static_cast<size_t>(g) * nq + i) * NP + b) * 4;
+      *reinterpret_cast<double2*>(out) = make_double2(rs, lo);
+      *reinterpret_cast<double2*>(out + 2) = make_double2(dg, 0.0);
+    }
+    s_sum[q][bl] = rs;
+    __syncthreads();
+    for (int c = 0; c < kGpC && i0 + c < nq; ++c) G += s_sum[c][bl];   // channels in ascending order
+    __syncthreads();
   }
+  if (q || b >= NP) return;
+  const double dt = tlen[g];   // length of the step into grid g
+  const size_t idx = static_cast<size_t>(g) * NP + b;
   Gamma[idx] = G;
   if (b < n) {
     double sn, cs;
@@ -180,19 +201,21 @@ __global__ void k_pack_chan(const double* __restrict__ Rcol, const double* __res
                          static_cast<float>(zdiag[idx]));
 }
 
-__global__ void k_max_gdt(const double* __restrict__ Gamma, const double* __restrict__ tlen, int M, int NP,
-                          double* __restrict__ out) {
+// (kGdtParts workgroups, one partial maximum each)
+constexpr int kGdtParts = 64;
+__global__ __launch_bounds__(256) void k_max_gdt(const double* __restrict__ Gamma, const double* __restrict__ tlen,
+                                                 int M, int NP, double* __restrict__ out) {
   __shared__ double red[256];
   double v = 0.0;
-  for (int64_t i = static_cast<int64_t>(NP) + threadIdx.x; i < static_cast<int64_t>(M) * NP; i += blockDim.x)
-    v = fmax(v, Gamma[i] * tlen[i / NP]);
+  for (int g = 1 + blockIdx.x; g < M; g += kGdtParts)
+    for (int b = threadIdx.x; b < NP; b += blockDim.x) v = fmax(v, Gamma[static_cast<size_t>(g) * NP + b] * tlen[g]);
   red[threadIdx.x] = v;
   __syncthreads();
   for (int o = blockDim.x / 2; o > 0; o >>= 1) {
     if (threadIdx.x < o) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + o]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = red[0];
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
 }
 
 aqt_status check_step_decay(aqt_ctx* ctx, int precision) {
@@ -239,18 +262,25 @@ aqt_status finish_tables(aqt_ctx* ctx) {
       ctx->Rcol.reserve(cnt * ctx->tab_nch * 4 * sizeof(double)) != hipSuccess ||
       ctx->ehalf.reserve(cnt * sizeof(double)) != hipSuccess)
     return ctx->fail(AQT_ENOMEM, "table allocation failed");
-  hipLaunchKernelGGL(k_gamma_phase, dim3(blocks_for(cnt)), dim3(256), 0, ctx->stream, ctx->E.as<double>(),
-                     ctx->shift.as<double>(), ctx->R.as<double>(), ctx->M, ctx->NP, ctx->n, ctx->tab_nch, ctx->tlen.as<double>(), ctx->Gamma.as<double>(),
-                     ctx->Rcol.as<double>(), ctx->ehalf.as<double>(), ctx->dre.as<double>(), ctx->dim.as<double>());
+  for (int g0 = 0; g0 < M; g0 += 65535) {   // grid y
+    const size_t o = static_cast<size_t>(g0) * ctx->NP;
+    hipLaunchKernelGGL(k_gamma_phase, dim3((ctx->NP + 63) / 64, std::min(65535, M - g0)), dim3(256), 0, ctx->stream,
+                       ctx->E.as<double>() + o, ctx->shift.as<double>() + o,
+                       ctx->R.as<double>() + o * ctx->tab_nch * ctx->NP, ctx->NP, ctx->n, ctx->tab_nch,
+                       ctx->tlen.as<double>() + g0, ctx->Gamma.as<double>() + o, ctx->Rcol.as<double>() + o * ctx->tab_nch * 4,
+                       ctx->ehalf.as<double>() + o, ctx->dre.as<double>() + o, ctx->dim.as<double>() + o);
+  }
   AQT_HIP(ctx, hipGetLastError());
   {
     ScratchBuf mx(ctx);
-    if (mx.reserve(sizeof(double)) != hipSuccess) return ctx->fail(AQT_ENOMEM, "table allocation failed");
-    hipLaunchKernelGGL(k_max_gdt, dim3(1), dim3(256), 0, ctx->stream, ctx->Gamma.as<double>(), ctx->tlen.as<double>(),
+    double part[kGdtParts];
+    if (mx.reserve(sizeof(part)) != hipSuccess) return ctx->fail(AQT_ENOMEM, "table allocation failed");
+    hipLaunchKernelGGL(k_max_gdt, dim3(kGdtParts), dim3(256), 0, ctx->stream, ctx->Gamma.as<double>(), ctx->tlen.as<double>(),
                        ctx->M, ctx->NP, mx.as<double>());
     AQT_HIP(ctx, hipGetLastError());
-    AQT_HIP(ctx, hipMemcpyAsync(&ctx->max_gdt, mx.p, sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+    AQT_HIP(ctx, hipMemcpyAsync(part, mx.p, sizeof(part), hipMemcpyDeviceToHost, ctx->stream));
     AQT_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    ctx->max_gdt = *std::max_element(part, part + kGdtParts);
   }
   ctx->packed_for = -1;
   ctx->fix_prec = -1;
