@@ -132,43 +132,30 @@ __device__ __forceinline__ f4 mfma_k4(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Round-to-nearest-even FP32 -> BF16 bits (inputs are finite).
-__device__ __forceinline__ uint32_t bf16_bits(float x) {
-  uint32_t u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
+// Round-to-nearest-even FP32 -> BF16 of two values (inputs are finite), the first in the low half.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pair(float x, float y) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{x, y}), bf16x2));
 }
+__device__ __forceinline__ float bf16_low(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_high(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// hi/lo BF16 split of 8 floats: x ~ hi + lo with |x - hi - lo| <= 2^-17 |x|.
-__device__ __forceinline__ void split8(const float* x, bf16x8& hi, bf16x8& lo) {
-  uint32_t h[4], l[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    uint32_t h0 = bf16_bits(x[2 * j]), h1 = bf16_bits(x[2 * j + 1]);
-    float r0 = x[2 * j] - __uint_as_float(h0 << 16);
-    float r1 = x[2 * j + 1] - __uint_as_float(h1 << 16);
-    h[j] = h0 | (h1 << 16);
-    l[j] = bf16_bits(r0) | (bf16_bits(r1) << 16);
-  }
-  uint4 hv = make_uint4(h[0], h[1], h[2], h[3]);
-  uint4 lv = make_uint4(l[0], l[1], l[2], l[3]);
-  hi = __builtin_bit_cast(bf16x8, hv);
-  lo = __builtin_bit_cast(bf16x8, lv);
-}
-
-// hi/lo BF16 split of 4 floats, packed as two 64-bit words.
-__device__ __forceinline__ void split4(const float* x, s16x4& hi, s16x4& lo) {
-  uint32_t h[2], l[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    uint32_t h0 = bf16_bits(x[2 * j]), h1 = bf16_bits(x[2 * j + 1]);
-    float r0 = x[2 * j] - __uint_as_float(h0 << 16);
-    float r1 = x[2 * j + 1] - __uint_as_float(h1 << 16);
-    h[j] = h0 | (h1 << 16);
-    l[j] = bf16_bits(r0) | (bf16_bits(r1) << 16);
-  }
-  hi = __builtin_bit_cast(s16x4, make_uint2(h[0], h[1]));
-  lo = __builtin_bit_cast(s16x4, make_uint2(l[0], l[1]));
+// hi/lo BF16 split of 4 floats: x ~ hi + lo with |x - hi - lo| <= 2^-17 |x|.  x holds the rest
+// x - hi - lo on return; it has at most 8 significant bits, so hi, lo and the rest as three
+// BF16 words are x exactly.
+__device__ __forceinline__ void split4(float* x, uint2& hi, uint2& lo) {
+#pragma clang fp contract(off)
+  hi = make_uint2(bf16_pair(x[0], x[1]), bf16_pair(x[2], x[3]));
+  x[0] -= bf16_low(hi.x);
+  x[1] -= bf16_high(hi.x);
+  x[2] -= bf16_low(hi.y);
+  x[3] -= bf16_high(hi.y);
+  lo = make_uint2(bf16_pair(x[0], x[1]), bf16_pair(x[2], x[3]));
+  x[0] -= bf16_low(lo.x);
+  x[1] -= bf16_high(lo.x);
+  x[2] -= bf16_low(lo.y);
+  x[3] -= bf16_high(lo.y);
 }
 
 // A-operand fragments of Delta read by one load per lane: 16 bytes of consecutive k
@@ -221,32 +208,108 @@ constexpr int prefetch_depth() {
 }
 
 // ----------------------------------------------------------- jump handler --
-// Tile layout in LDS: S[q][c][row] holds column tile q (8 trajectories) column-
-// major; column c = (t & 7) + 8 * part carries the real (part 0) or imaginary
-// (part 1) part of local trajectory t = 8 q + (c & 7).  Columns are padded so that an MFMA
-// operand read (row 4 k + lane / 16 of column lane % 16) meets distinct banks: 4 floats, and 2
-// doubles, which are read half a wavefront at a time (4 doubles: two-way conflicts).
+// Tile layout in LDS: S[q] holds column tile q (8 trajectories) column-major; column
+// c = (t & 7) + 8 * part carries the real (part 0) or imaginary (part 1) part of local
+// trajectory t = 8 q + (c & 7).
+// Columns are padded so that an MFMA operand read (row 4 k + lane / 16 of column lane % 16)
+// meets distinct banks: 4 floats, and 2 doubles, which are read half a wavefront at a time
+// (4 doubles: two-way conflicts).
 template <class T>
 constexpr int col_pad() {
   return sizeof(T) == 8 ? 2 : 4;
 }
+// One trajectory's column, by level.
+template <class T>
+struct PlainCol {
+  T* p;
+  __device__ __forceinline__ T get(int x) const { return p[x]; }
+  __device__ __forceinline__ void set(int x, T v) const { p[x] = v; }
+};
+template <int NP, class T>
+struct PlainTile {
+  using Col = PlainCol<T>;
+  T c[16][NP + col_pad<T>()];
+  __device__ __forceinline__ Col col(int i) { return Col{&c[i][0]}; }
+  // four rows of one column per lane: consecutive ones in the FP32 layout, else every fourth
+  template <class Acc>
+  __device__ __forceinline__ void load4(int lane, int rt, Acc& v) const {
+    if constexpr (sizeof(T) == 4) {
+      v = *reinterpret_cast<const Acc*>(&c[lane & 15][rt * 16 + 4 * (lane >> 4)]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = c[lane & 15][rt * 16 + (lane >> 4) + 4 * i];
+    }
+  }
+  template <class Acc>
+  __device__ __forceinline__ void store4(int lane, int rt, const Acc& v) {
+    if constexpr (sizeof(T) == 4) {
+      *reinterpret_cast<Acc*>(&c[lane & 15][rt * 16 + 4 * (lane >> 4)]) = v;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[lane & 15][rt * 16 + (lane >> 4) + 4 * i] = v[i];
+    }
+  }
+};
+// BF16 runs keep every amplitude as the three BF16 words of split4, whose sum it is: the
+// products read their B operand as it stands.  (Splitting FP32 amplitudes in the k loop had
+// every wavefront split the whole tile every step: 14000 of 40000 cycles at 256 levels with 40
+// trajectories, where the epilogue, once per amplitude, takes 1800; FP32 words beside the split
+// ones would not fit the LDS.)  8 words of padding spread the 16-byte operand reads.
+template <int NP>
+struct SplitCol {
+  static constexpr int kWord = 16 * (NP + 8);   // distance between the words of an amplitude
+  uint16_t* p;
+  static __device__ __forceinline__ float up(uint16_t w) { return __uint_as_float(static_cast<uint32_t>(w) << 16); }
+  __device__ __forceinline__ float get(int x) const { return (up(p[x]) + up(p[x + kWord])) + up(p[x + 2 * kWord]); }
+  __device__ __forceinline__ void set(int x, float v) const {
+    // (a product in v must not fuse with the subtraction: the words have to add up to v as rounded)
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint16_t w = static_cast<uint16_t>(bf16_pair(v, 0.f));
+      p[x + k * kWord] = w;
+      v -= up(w);
+    }
+  }
+};
+template <int NP>
+struct SplitTile {
+  using Col = SplitCol<NP>;
+  uint16_t w[3][16][NP + 8];
+  __device__ __forceinline__ Col col(int i) { return Col{&w[0][i][0]}; }
+  __device__ __forceinline__ void load4(int lane, int rt, f4& v) const {
+    const int r = rt * 16 + 4 * (lane >> 4);
+    uint2 u[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) u[k] = *reinterpret_cast<const uint2*>(&w[k][lane & 15][r]);
+    v[0] = (bf16_low(u[0].x) + bf16_low(u[1].x)) + bf16_low(u[2].x);
+    v[1] = (bf16_high(u[0].x) + bf16_high(u[1].x)) + bf16_high(u[2].x);
+    v[2] = (bf16_low(u[0].y) + bf16_low(u[1].y)) + bf16_low(u[2].y);
+    v[3] = (bf16_high(u[0].y) + bf16_high(u[1].y)) + bf16_high(u[2].y);
+  }
+  __device__ __forceinline__ void store4(int lane, int rt, const f4& v) {
+    const int r = rt * 16 + 4 * (lane >> 4);
+    float x[4] = {v[0], v[1], v[2], v[3]};
+    uint2 hi, lo;
+    split4(x, hi, lo);
+    *reinterpret_cast<uint2*>(&w[0][lane & 15][r]) = hi;
+    *reinterpret_cast<uint2*>(&w[1][lane & 15][r]) = lo;
+    *reinterpret_cast<uint2*>(&w[2][lane & 15][r]) = make_uint2(bf16_pair(x[0], x[1]), bf16_pair(x[2], x[3]));
+  }
+};
+template <int NP, class Mode>
+using TileCols = typename std::conditional<Mode::KC == 32, SplitTile<NP>, PlainTile<NP, typename Mode::T>>::type;
+
 constexpr int kStepTables = 5;
 // Wavefronts per workgroup.  Eight (two per SIMD) let one wave's LDS and load waits
 // hide behind the other's MFMAs where each wave still has a large share of the
-// GEMM (>= 128 levels, FP32/FP64 and the batched kernel); small tiles and the
-// register-heavy BF16 path at 256 levels keep four.
+// GEMM (BF16, 256 levels, 40 trajectories, before the operand loads were pinned: 12.3 us a step
+// against 19.3 with four); 64 levels
+// keep four.
 template <int NP, class Mode>
 constexpr int waves_for() {
-  return (NP >= 128 && Mode::KC == 4) ? 8 : 4;
+  return NP >= 128 ? 8 : 4;
 }
-template <int NP, class T>
-using TileCols = T[16][NP + col_pad<T>()];
-
-template <int NP, class T>
-__device__ __forceinline__ T& amp(TileCols<NP, T>* S, int t, int part, int row) {
-  return S[t >> 3][(t & 7) + 8 * part][row];
-}
-
 // Exchange with lane ^ 8 (the other part of the same amplitude) by DPP row
 // rotation: within each row of 16 lanes, rotating by 8 maps lane i to i ^ 8.
 __device__ __forceinline__ float xor8(float v) {
@@ -481,15 +544,15 @@ __device__ constexpr H newton_tol() {
 // precision runs take the crossing time, the channel scans and the renormalisation
 // in FP32 (native exponentials, 32-bit shuffles).  The crossing test itself and
 // the observable sums stay in FP64 in every mode.
-// cre, cim: the trajectory's column in LDS (real and imaginary parts by level).  WAVE: the
+// cre, cim: the trajectory's columns in LDS (real and imaginary parts by level).  WAVE: the
 // one-wavefront kernel, which hands over Gamma and e^{G dt / 2} of this lane's levels in
 // registers (tw) and keeps the Philox cache filled itself (rc.b = end of the filled blocks).
 template <class T, int PL>
 struct LaneTables {
   T G[PL], up[PL];
 };
-template <int NP, class T, bool STAGED, bool WAVE>
-__device__ void finish_crossing(CArgs& args, int g, int t, int64_t jloc, T* cre, T* cim,
+template <int NP, class T, bool STAGED, bool WAVE, class Col>
+__device__ void finish_crossing(CArgs& args, int g, int t, int64_t jloc, Col cre, Col cim,
                                 const double* s_r, double* s_rn, int* s_m, int* s_cnt, int* s_net, double* s_p,
                                 int* s_kind, RngCache rc, bool ahead, int gsz, const double* tg, const float4* chs,
                                 const LaneTables<T, NP / seg_width<NP>()>& tw) {
@@ -520,8 +583,8 @@ __device__ void finish_crossing(CArgs& args, int g, int t, int64_t jloc, T* cre,
       G[j] = static_cast<H>(Gam[x]);
       up[j] = static_cast<H>(Eh[x]);
     }
-    sr[j] = cre[x];
-    si[j] = cim[x];
+    sr[j] = cre.get(x);
+    si[j] = cim.get(x);
   }
   double r = s_r[t];
   int m = s_m[t];
@@ -826,8 +889,8 @@ __device__ void finish_crossing(CArgs& args, int g, int t, int64_t jloc, T* cre,
     const double w2 = xr * xr + xi * xi;
     pt += w2;
     if (x < gsz) pg += w2;
-    cre[x] = cr[j];
-    cim[x] = ci[j];
+    cre.set(x, cr[j]);
+    cim.set(x, ci[j]);
   }
   pg = seg_sum<SEG>(pg);
   pt = seg_sum<SEG>(pt);
@@ -867,19 +930,15 @@ constexpr bool stage_channels() {
 }
 
 // --------------------------------------------------------------- kernel ----
-// Work split of the overlap GEMM over the WV wavefronts: with WV or more row
-// tiles each wave owns the row tiles rt = wave (mod WV) for every column tile
-// (one A fragment feeds TQ MFMAs); with fewer, waves take (row tile, column
-// tile) pairs.  The k loop is outermost so each wave keeps UPW*QG independent
-// accumulator chains in flight.
+// Work split of the overlap GEMM over the WV wavefronts: each wave owns the row tiles
+// rt = wave (mod WV) for every column tile (one A fragment feeds TQ MFMAs).  The k loop is
+// outermost so each wave keeps UPW*TQ independent accumulator chains in flight.
 template <int NP, int TQ, class Mode, int WV>
 struct TileShared {
   using T = typename Mode::T;
-  static constexpr int NRT = NP / 16;
   static constexpr int TT = 8 * TQ;
-  static constexpr int NSLOT = (NRT >= WV) ? WV : NRT;   // partial squared norms per trajectory
-  TileCols<NP, T> S[TQ];
-  double nu[NSLOT][TT];   // partial squared norms, accumulated in FP64
+  TileCols<NP, Mode> S[TQ];
+  double nu[WV][TT];   // partial squared norms per wavefront, accumulated in FP64
   double r[2][TT];   // waiting-time thresholds: read from r[g & 1], written to r[(g + 1) & 1]
   double p[TT];
   int m[TT], cnt[TT], net[TT];
@@ -902,9 +961,8 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
   using Acc = typename Mode::Acc;
   constexpr int NRT = NP / 16;
   constexpr int TT = 8 * TQ;
-  constexpr int QG = (NRT >= WV) ? TQ : 1;         // column tiles per work unit
-  constexpr int NUNITS = NRT * (TQ / QG);
-  constexpr int UPW = (NUNITS + WV - 1) / WV;      // units per wave
+  static_assert(NRT % WV == 0, "every wavefront owns the same number of row tiles");
+  constexpr int UPW = NRT / WV;             // row tiles per wave
   constexpr int NKC = NP / Mode::KC;
   constexpr int FW = frag_chunks<Mode>();   // k chunks per fragment load
   constexpr int NKG = NKC / FW;
@@ -912,7 +970,6 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
 
   auto& S = sh.S;
   auto& s_nu = sh.nu;
-  constexpr int NSLOT = TileShared<NP, TQ, Mode, WV>::NSLOT;
   double* s_p = sh.p;
   int* s_m = sh.m;
   int* s_cnt = sh.cnt;
@@ -938,22 +995,10 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
   if (tid == 0) sh.nrfl = 0;
   if (wave == WV - 1) rng_refill(a, tb, TT, nullptr, nullptr, rc, lane);   // m = 0: blocks 0 and 1
 
-  int rt_u[UPW], q0_u[UPW];
-  bool ok_u[UPW];
+  int rt_u[UPW];
 #pragma unroll
-  for (int u = 0; u < UPW; ++u) {
-    const int unit = wave + WV * u;
-    ok_u[u] = (NUNITS % WV == 0) || unit < NUNITS;
-    rt_u[u] = unit % NRT;
-    q0_u[u] = (unit / NRT) * QG;
-  }
-  Acc acc[UPW][QG];
-  // with >= WV row tiles every unit covers all column tiles (q0 = 0) and each wave
-  // keeps one norm partial per trajectory (NSLOT = WV); otherwise units are
-  // (row tile, column tile) pairs and the partials are per row tile
-  constexpr bool kSharedQ = (NRT >= WV);
-  static_assert(NSLOT == (kSharedQ ? WV : NRT), "norm slots follow the work split");
-#define q0(u) (kSharedQ ? 0 : q0_u[u])
+  for (int u = 0; u < UPW; ++u) rt_u[u] = (wave + WV * u) % NRT;   // (the modulo shows the range: 32-bit offsets)
+  Acc acc[UPW][TQ];
   // fragment load (g, row tile, k group) lives at ((g * NRT + rt) * NKG + k) * 64 + lane
   size_t fbase[UPW];
 #pragma unroll
@@ -968,27 +1013,9 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
     for (int s2 = 0; s2 < PF; ++s2)
 #pragma unroll
       for (int u = 0; u < UPW; ++u)
-        if (ok_u[u]) ring[s2][u] = load_frag<Mode>(a, frag_index(2, u, s2));
+        ring[s2][u] = load_frag<Mode>(a, frag_index(2, u, s2));
   }
 
-  // Accumulator <-> LDS: four rows of one column per lane (consecutive rows in
-  // the FP32 layouts, one 16-byte access).
-  auto acc_load = [&](int q, int rt, Acc& v) {
-    if constexpr (sizeof(T) == 4) {
-      v = *reinterpret_cast<const Acc*>(&S[q][lc][rt * 16 + 4 * (lane >> 4)]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = S[q][lc][rt * 16 + Mode::row(lane, i)];
-    }
-  };
-  auto acc_store = [&](int q, int rt, const Acc& v) {
-    if constexpr (sizeof(T) == 4) {
-      *reinterpret_cast<Acc*>(&S[q][lc][rt * 16 + 4 * (lane >> 4)]) = v;
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) S[q][lc][rt * 16 + Mode::row(lane, i)] = v[i];
-    }
-  };
   // The accumulators keep C between steps (the identity split starts from C);
   // only column tiles touched by the jump handler are reloaded from LDS.
   unsigned dirty = 0;
@@ -1014,24 +1041,20 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
     // ---- 1. C + Delta C (or the initial state at g = 1)
     if (g == 1) {
 #pragma unroll
-      for (int u = 0; u < UPW; ++u) {
-        if (!ok_u[u]) continue;
+      for (int u = 0; u < UPW; ++u)
 #pragma unroll
-        for (int qq = 0; qq < QG; ++qq)
+        for (int qq = 0; qq < TQ; ++qq)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int row = rt_u[u] * 16 + Mode::row(lane, i);
             acc[u][qq][i] = part ? T(0) : static_cast<T>(a.cinit[row]);
           }
-      }
     } else if (dirty) {
 #pragma unroll
-      for (int u = 0; u < UPW; ++u) {
-        if (!ok_u[u]) continue;
+      for (int u = 0; u < UPW; ++u)
 #pragma unroll
-        for (int qq = 0; qq < QG; ++qq)
-          if ((dirty >> (q0(u) + qq)) & 1u) acc_load(q0(u) + qq, rt_u[u], acc[u][qq]);
-      }
+        for (int qq = 0; qq < TQ; ++qq)
+          if ((dirty >> qq) & 1u) S[qq].load4(lane, rt_u[u], acc[u][qq]);
     }
     // the step's phase factors, loaded ahead of the GEMM (used by the epilogue)
     T dpre[UPW][4], dpim[UPW][4];
@@ -1061,10 +1084,10 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
       chv[k] = (ch_on && f < nch_e) ? a.chf[static_cast<size_t>(g) * nch_e + f] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     if (g > 1) {
-      T bnx[QG];
-      if constexpr (Mode::KC == 4 && kSharedQ) {
+      T bnx[TQ];
+      if constexpr (Mode::KC == 4) {
 #pragma unroll
-        for (int qq = 0; qq < QG; ++qq) bnx[qq] = S[qq][lc][lane >> 4];
+        for (int qq = 0; qq < TQ; ++qq) bnx[qq] = S[qq].c[lc][lane >> 4];
       }
       // two wavefronts share each SIMD, and with equal priorities they issue so that one
       // finishes its share early and leaves the other to run the tail of the GEMM alone
@@ -1072,6 +1095,9 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
       // the end (waves 0-3 measured 0.6% faster than waves 4-7 in FP32, 0.7% in FP64
       // against equal priorities).
       if (WV == 8 && wave < 4) __builtin_amdgcn_s_setprio(1);
+      // (unrolled: left to itself the compiler keeps a loop for the widest FP32 tile, whose
+      // rotated ring waits on loads just issued; 25.7 us against 24.1)
+#pragma unroll
       for (int kg = 0; kg < NKG; kg += PF) {
 #pragma unroll
         for (int s2 = 0; s2 < PF; ++s2) {
@@ -1085,95 +1111,48 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
           const int kk = kn < NKG ? kn : kn - NKG;
 #pragma unroll
           for (int u = 0; u < UPW; ++u)
-            if (ok_u[u]) ring[s2][u] = load_frag<Mode>(a, frag_index(gn, u, kk));
-          if constexpr (Mode::KC == 4 && kSharedQ) {
+            ring[s2][u] = load_frag<Mode>(a, frag_index(gn, u, kk));
+          // The unrolled loop is one block, in which the scheduler moves these loads down to the
+          // products that use them: pinned, 256 levels take 6.9 us a step against 8.0 with 8
+          // FP32 trajectories, 23.3 against 24.2 with 40, and 6.6 against 9.1 with 16 in BF16.
+          // FP64 (24 trajectories) already keeps them apart, and only loses freedom (0.7%).
+          if constexpr (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
+          if constexpr (Mode::KC == 4) {
             // B for this chunk was read one chunk ahead; read the next one now (on
             // the last chunk that is chunk 0 again: unused)
 #pragma unroll
             for (int w = 0; w < FW; ++w) {
               const int k = (kg + s2) * FW + w;
-              T bcur[QG];
+              T bcur[TQ];
 #pragma unroll
-              for (int qq = 0; qq < QG; ++qq) bcur[qq] = bnx[qq];
-              const int krn = (4 * (k + 1) & (NP - 1)) + (lane >> 4);
+              for (int qq = 0; qq < TQ; ++qq) bcur[qq] = bnx[qq];
+              const bool wraps = s2 == PF - 1 && w == FW - 1;   // only here: fixed offsets elsewhere
+              const int krn = (wraps ? 4 * (k + 1) & (NP - 1) : 4 * (k + 1)) + (lane >> 4);
 #pragma unroll
-              for (int qq = 0; qq < QG; ++qq) bnx[qq] = S[qq][lc][krn];
-#pragma unroll
-              for (int u = 0; u < UPW; ++u)
-#pragma unroll
-                for (int qq = 0; qq < QG; ++qq) acc[u][qq] = mfma_k4(av[u].v[w], bcur[qq], acc[u][qq]);
-            }
-          } else if constexpr (Mode::KC == 4) {
-#pragma unroll
-            for (int w = 0; w < FW; ++w) {
-              const int krow = 4 * ((kg + s2) * FW + w) + (lane >> 4);
-              T bv[UPW][QG];
+              for (int qq = 0; qq < TQ; ++qq) bnx[qq] = S[qq].c[lc][krn];
 #pragma unroll
               for (int u = 0; u < UPW; ++u)
 #pragma unroll
-                for (int qq = 0; qq < QG; ++qq)
-                  bv[u][qq] = (u == 0 || !kSharedQ) ? S[q0(u) + qq][lc][krow] : bv[0][qq];
-#pragma unroll
-              for (int u = 0; u < UPW; ++u) {
-                if (!ok_u[u]) continue;
-#pragma unroll
-                for (int qq = 0; qq < QG; ++qq) acc[u][qq] = mfma_k4(av[u].v[w], bv[u][qq], acc[u][qq]);
-              }
-            }
-          } else if constexpr (Mode::KC == 16) {
-            const int k0 = 16 * (kg + s2) + 4 * (lane >> 4);
-#pragma unroll
-            for (int u = 0; u < UPW; ++u) {
-              if (!ok_u[u]) continue;
-              const s16x4 ah = __builtin_bit_cast(s16x4, av[u].h);
-              const s16x4 al = __builtin_bit_cast(s16x4, av[u].l);
-#pragma unroll
-              for (int qq = 0; qq < QG; ++qq) {
-                float xv[4];
-                *reinterpret_cast<float4*>(xv) = *reinterpret_cast<const float4*>(&S[q0(u) + qq][lc][k0]);
-                s16x4 bh, bl;
-                split4(xv, bh, bl);
-                Acc c = acc[u][qq];
-                c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(al, bh, c, 0, 0, 0);
-                acc[u][qq] = c;
-              }
+                for (int qq = 0; qq < TQ; ++qq) acc[u][qq] = mfma_k4(av[u].v[w], bcur[qq], acc[u][qq]);
             }
           } else {
             const int k0 = 32 * (kg + s2) + 8 * (lane >> 4);
-            // B split once per column tile when every unit shares the column tiles
-            bf16x8 bh[kSharedQ ? QG : 1], bl[kSharedQ ? QG : 1];
-            if constexpr (kSharedQ) {
+            bf16x8 bh[TQ], bl[TQ];
 #pragma unroll
-              for (int qq = 0; qq < QG; ++qq) {
-                float xv[8];
-                *reinterpret_cast<float4*>(xv) = *reinterpret_cast<const float4*>(&S[qq][lc][k0]);
-                *reinterpret_cast<float4*>(xv + 4) = *reinterpret_cast<const float4*>(&S[qq][lc][k0 + 4]);
-                split8(xv, bh[qq], bl[qq]);
-              }
+            for (int qq = 0; qq < TQ; ++qq) {
+              bh[qq] = *reinterpret_cast<const bf16x8*>(&S[qq].w[0][lc][k0]);
+              bl[qq] = *reinterpret_cast<const bf16x8*>(&S[qq].w[1][lc][k0]);
             }
 #pragma unroll
             for (int u = 0; u < UPW; ++u) {
-              if (!ok_u[u]) continue;
               const bf16x8 ah = __builtin_bit_cast(bf16x8, av[u].h);
               const bf16x8 al = __builtin_bit_cast(bf16x8, av[u].l);
 #pragma unroll
-              for (int qq = 0; qq < QG; ++qq) {
-                bf16x8 h, l;
-                if constexpr (kSharedQ) {
-                  h = bh[qq];
-                  l = bl[qq];
-                } else {
-                  float xv[8];
-                  *reinterpret_cast<float4*>(xv) = *reinterpret_cast<const float4*>(&S[q0(u) + qq][lc][k0]);
-                  *reinterpret_cast<float4*>(xv + 4) = *reinterpret_cast<const float4*>(&S[q0(u) + qq][lc][k0 + 4]);
-                  split8(xv, h, l);
-                }
+              for (int qq = 0; qq < TQ; ++qq) {
                 Acc c = acc[u][qq];
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, h, c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, l, c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, h, c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[qq], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[qq], c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[qq], c, 0, 0, 0);
                 acc[u][qq] = c;
               }
             }
@@ -1198,18 +1177,17 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
       }
     }
     __syncthreads();   // every wave has finished reading S
-    // ---- 2. C' = d o C and the squared norms (partial sums per wave or row tile).
+    // ---- 2. C' = d o C and the squared norms (partial sums per wave).
     // The squares of state-precision amplitudes are exact in FP64 and every sum of
     // them (per lane, across lanes, across slots) is taken in FP64, so the threshold
     // test sees the norm of the stored state to FP64 rounding whatever the state
     // precision: a compensated norm, not a state-precision running sum.
     {
-      double nacc[QG];
+      double nacc[TQ];
 #pragma unroll
-      for (int qq = 0; qq < QG; ++qq) nacc[qq] = 0.0;
+      for (int qq = 0; qq < TQ; ++qq) nacc[qq] = 0.0;
 #pragma unroll
       for (int u = 0; u < UPW; ++u) {
-        if (!ok_u[u]) continue;
         const int rt = rt_u[u];
         T drv[4], div[4];
 #pragma unroll
@@ -1218,7 +1196,7 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
           div[i] = dpim[u][i];
         }
 #pragma unroll
-        for (int qq = 0; qq < QG; ++qq) {
+        for (int qq = 0; qq < TQ; ++qq) {
           double nrm = 0.0;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -1230,26 +1208,17 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
             const double cd = static_cast<double>(c);
             nrm = fma(cd, cd, nrm);
           }
-          acc_store(q0(u) + qq, rt, acc[u][qq]);
-          if constexpr (kSharedQ) {
-            nacc[qq] += nrm;
-          } else {
-            nrm += xor8(nrm);
-            nrm = swap_add<16>(nrm);
-            nrm = swap_add<32>(nrm);
-            if (lane < 8) s_nu[rt][(q0(u) + qq) * 8 + lane] = nrm;
-          }
+          S[qq].store4(lane, rt, acc[u][qq]);
+          nacc[qq] += nrm;
         }
       }
-      if constexpr (kSharedQ) {
 #pragma unroll
-        for (int qq = 0; qq < QG; ++qq) {
-          double nrm = nacc[qq];
-          nrm += xor8(nrm);
-          nrm = swap_add<16>(nrm);
-          nrm = swap_add<32>(nrm);
-          if (lane < 8) s_nu[wave][qq * 8 + lane] = nrm;
-        }
+      for (int qq = 0; qq < TQ; ++qq) {
+        double nrm = nacc[qq];
+        nrm += xor8(nrm);
+        nrm = swap_add<16>(nrm);
+        nrm = swap_add<32>(nrm);
+        if (lane < 8) s_nu[wave][qq * 8 + lane] = nrm;
       }
     }
     __syncthreads();
@@ -1268,18 +1237,20 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
       const bool valid = lane < TT && tb + lane < a.K;
       if (lane < TT) {
 #pragma unroll
-        for (int sl = 0; sl < NSLOT; ++sl) nu += s_nu[sl][lane];
+        for (int sl = 0; sl < WV; ++sl) nu += s_nu[sl][lane];
         cross = valid && nu <= s_r[lane];
       }
       cmask = __ballot(cross);
       if (wave == 0 && lane < TT && !cross) {
         double gw = 0.0;
-        if (valid)
+        if (valid) {
+          const auto cre = S[lane >> 3].col(lane & 7), cim = S[lane >> 3].col((lane & 7) + 8);
           for (int row = 0; row < gsz; ++row) {
-            const double re = static_cast<double>(amp<NP, T>(S, lane, 0, row));
-            const double im = static_cast<double>(amp<NP, T>(S, lane, 1, row));
+            const double re = static_cast<double>(cre.get(row));
+            const double im = static_cast<double>(cim.get(row));
             gw += re * re + im * im;
           }
+        }
         s_p[lane] = valid ? gw / nu : 0.0;
         s_rn[lane] = s_r[lane];
       }
@@ -1300,9 +1271,9 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
           uint64_t mm = cmask;
           for (int k = 0; k < e; ++k) mm &= mm - 1;
           const int t = __builtin_ctzll(mm);
-          finish_crossing<NP, T, STAGED, false>(a, g, t, tb + t, &amp<NP, T>(S, t, 0, 0), &amp<NP, T>(S, t, 1, 0), s_r,
-                                                s_rn, s_m, s_cnt, s_net, s_p, s_kind, rc, ahead, gsz, &sh.tg[0][0],
-                                                ch_on ? sh.chs : nullptr, {});
+          finish_crossing<NP, T, STAGED, false>(a, g, t, tb + t, S[t >> 3].col(t & 7), S[t >> 3].col((t & 7) + 8),
+                                                s_r, s_rn, s_m, s_cnt, s_net, s_p, s_kind, rc, ahead, gsz,
+                                                &sh.tg[0][0], ch_on ? sh.chs : nullptr, {});
         }
       }
     }
@@ -1340,8 +1311,8 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
       const int t = e / a.n, x = e - t * a.n;
       const int64_t j = tb + t;
       if (j < a.K) {
-        a.final_state[(j * a.n + x) * 2 + 0] = static_cast<double>(amp<NP, T>(S, t, 0, x));
-        a.final_state[(j * a.n + x) * 2 + 1] = static_cast<double>(amp<NP, T>(S, t, 1, x));
+        a.final_state[(j * a.n + x) * 2 + 0] = static_cast<double>(S[t >> 3].col(t & 7).get(x));
+        a.final_state[(j * a.n + x) * 2 + 1] = static_cast<double>(S[t >> 3].col((t & 7) + 8).get(x));
       }
     }
   }
@@ -1349,7 +1320,6 @@ __device__ void run_tile(CArgs& a, int64_t tile, TileShared<NP, TQ, Mode, WV>& s
     atomicAdd(reinterpret_cast<unsigned long long*>(&a.jump_totals[tid]),
               static_cast<unsigned long long>(s_kind[tid]));
   __syncthreads();   // the shared tile state may be reused by the caller
-#undef q0
 #undef frag_index
 }
 
@@ -1542,9 +1512,8 @@ __device__ void run_wave(CArgs& a, int64_t tile, WaveShared<NP, TQ, Mode>& sh) {
             float x[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) x[i] = acc[q][rt][i];
-            s16x4 bh, bl;
-            split4(x, bh, bl);
-            const uint2 hh = __builtin_bit_cast(uint2, bh), ll = __builtin_bit_cast(uint2, bl);
+            uint2 hh, ll;
+            split4(x, hh, ll);
             h[rt][0] = hh.x;
             h[rt][1] = hh.y;
             l[rt][0] = ll.x;
@@ -1671,7 +1640,7 @@ __device__ void run_wave(CArgs& a, int64_t tile, WaveShared<NP, TQ, Mode>& sh) {
         }
         wave_lds_fence();
         if (seg < n)
-          finish_crossing<NP, T, false, true>(a, g, t, tb + t, &sh.X[seg][0][0], &sh.X[seg][1][0], sh.r, sh.r, sh.m,
+          finish_crossing<NP, T, false, true>(a, g, t, tb + t, PlainCol<T>{&sh.X[seg][0][0]}, PlainCol<T>{&sh.X[seg][1][0]}, sh.r, sh.r, sh.m,
                                               sh.cnt, sh.net, sh.p, sh.kind, rc, false, gsz, nullptr, nullptr, tw);
         wave_lds_fence();
 #pragma unroll
@@ -1954,8 +1923,8 @@ int explicit_tq(int NP, int precision, int tile) {
 // of widths whose sum covers the column tiles that fall to each CU.  Step times in
 // 0.1 us, measured at 256 levels on the 2000-point anneal: FP64 rises linearly (the GEMM
 // binds), so what counts is not to pay for idle columns: 10^4 trajectories (4.9 columns a
-// CU) take 3 + 2 (51.4 us a step) instead of three rounds of 2 (61.2); FP32 and BF16 gain
-// from width up to 5 (4096 trajectories on 256 tiles of 16: 13.2 us instead of 19.7 on 128
+// CU) take 3 + 2 (46.2 us a step) instead of three rounds of 2 (56.8); FP32 and BF16 gain
+// from width up to 5 (4096 FP32 trajectories on 256 tiles of 16: 11.1 us instead of 19.1 on 128
 // tiles of 32).
 TilePlan plan_tiles(int NP, int precision, int64_t K, int cus) {
   const int64_t cols = (K + 7) / 8;
@@ -1974,9 +1943,9 @@ TilePlan plan_tiles(int NP, int precision, int64_t K, int cus) {
     return plan;
   }
   constexpr int kW = 5;
-  static constexpr int kCost[3][kW] = {{117, 204, 310, 404, 1 << 20},   // FP64 (1, 2, 3, 4 columns)
-                                       {82, 132, 164, 197, 244},        // FP32
-                                       {65, 87, 114, 141, 169}};        // BF16
+  static constexpr int kCost[3][kW] = {{119, 189, 287, 380, 1 << 20},   // FP64 (1, 2, 3, 4 columns)
+                                       {69, 111, 151, 191, 233},        // FP32
+                                       {51, 66, 82, 97, 114}};          // BF16
   const int* cost = kCost[f64 ? 0 : (precision == AQT_FP32 ? 1 : 2)];
   int widest = 1;
   for (int w = 1; w <= kW; ++w)
