@@ -141,16 +141,10 @@ __device__ __forceinline__ void dot2_tile(const typename Mfma<T>::acc_t (&acc)[N
 template <int NP, int NC, int LD, class T>
 __device__ void gemm_dot2(const T* __restrict__ X, const T* B, const T* L1, const T* L2, double* part1,
                           double* part2) {
-  constexpr int RT = NP / 16, CT = NC / 16;
-  const int wave = threadIdx.x >> 6;
   const T* const Bs[1] = {B};
-  for (int rt = wave; rt < RT; rt += kGW) {
-    typename Mfma<T>::acc_t acc[1][CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[0][ct] = Mfma<T>::zero();
-    panel_mma<NP, NC, LD, T, 1>(X, rt, Bs, acc);
+  panel_mma<NP, NC, LD, T, 1>(X, Bs, [&](int, int rt, const typename Mfma<T>::acc_t (&acc)[1][NC / 16]) {
     dot2_tile<NP, NC, LD, T>(acc[0], rt, L1, L2, part1, part2);
-  }
+  });
 }
 
 // Row tiles of an NP-row product per wave.
@@ -164,21 +158,15 @@ template <int NP, int NC, int LD, class T>
 __device__ void gemm_dot2_pair(const T* __restrict__ X, const T* B, const T* A, const T* L1, const T* L2,
                                double* part1, double* part2, bool dotB,
                                typename Mfma<T>::acc_t (&accA)[rows_per_wave<NP>()][NC / 16]) {
-  constexpr int RT = NP / 16, CT = NC / 16;
-  const int wave = threadIdx.x >> 6;
   const T* const Bs[2] = {B, A};
-  int i = 0;
-  for (int rt = wave; rt < RT; rt += kGW, ++i) {
-    typename Mfma<T>::acc_t acc[2][CT];
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc[b][ct] = Mfma<T>::zero();
-    panel_mma<NP, NC, LD, T, 2>(X, rt, Bs, acc);
+  panel_mma<NP, NC, LD, T, 2>(X, Bs, [&](int i, int rt, const typename Mfma<T>::acc_t (&acc)[2][NC / 16]) {
     if (dotB) dot2_tile<NP, NC, LD, T>(acc[0], rt, L1, L2, part1, part2);
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) accA[i][ct] = acc[1][ct];
-  }
+    for (int j = 0; j < rows_per_wave<NP>(); ++j)   // (i is no constant: no indexed registers)
+      if (j == i)
+#pragma unroll
+        for (int ct = 0; ct < NC / 16; ++ct) accA[j][ct] = acc[1][ct];
+  });
 }
 
 template <int NP, int NC, int LD, class T>
@@ -606,27 +594,34 @@ __global__ __launch_bounds__(kGThreads) void k_grad(GradArgs a) {
       else
         gemm_dot2<NP, NC, LD, T>(Xg, PA, LP, LI, &sh.part[wave][0][0], &sh.part[wave][1][0]);
       __syncthreads();
-      for (int t = tid; t < TT; t += kGThreads) {
+      // (all loads before the first store: one after the other, the ten sums of a trajectory
+      // kept one wave 20000 cycles of a 256-level step)
+      for (int ta = tid; ta < 2 * TT; ta += kGThreads) {
+        const int t = ta % TT, adj = ta / TT;
         if (!active(t)) continue;
         const double u = a.sg[g] * (a.nctrl - 1);
         const int j = std::min(static_cast<int>(floor(u)), a.nctrl - 2);
         const double fr = u - j;
-        for (int adj = 0; adj < 2; ++adj) {
-          double pa = 0.0, pb = 0.0;
-          for (int w = 0; w < kGW; ++w) {
-            pa += sh.part[w][adj][t];
-            pb += sh.part[w][2 + adj][t];
-          }
-          double xa[2];
-          for (int dir = 0; dir < 2; ++dir) xa[dir] = sh.S[t][3 * adj + dir] + 2.0 * a.xc[3 * g + dir] * (pb - pa);
-          double* o = a.out + traj(t) * a.ostride + adj * (P + 1);
-          o[1 + j] += (1.0 - fr) * xa[0];
-          o[2 + j] += fr * xa[0];
-          o[1 + a.nctrl + j] += (1.0 - fr) * xa[1];
-          o[2 + a.nctrl + j] += fr * xa[1];
-          o[P] += sh.S[t][3 * adj + 2];
-          if (g == a.M - 1) o[0] = adj ? 1.0 : sh.f[t];
+        double* o = a.out + traj(t) * a.ostride + adj * (P + 1);
+        double oA0 = o[1 + j], oA1 = o[2 + j], oB0 = o[1 + a.nctrl + j], oB1 = o[2 + a.nctrl + j], oe = o[P];
+        double pa = 0.0, pb = 0.0;
+        for (int w = 0; w < kGW; ++w) {
+          pa += sh.part[w][adj][t];
+          pb += sh.part[w][2 + adj][t];
         }
+        double xa[2];
+        for (int dir = 0; dir < 2; ++dir) xa[dir] = sh.S[t][3 * adj + dir] + 2.0 * a.xc[3 * g + dir] * (pb - pa);
+        oA0 += (1.0 - fr) * xa[0];
+        oA1 += fr * xa[0];
+        oB0 += (1.0 - fr) * xa[1];
+        oB1 += fr * xa[1];
+        oe += sh.S[t][3 * adj + 2];
+        o[1 + j] = oA0;
+        o[2 + j] = oA1;
+        o[1 + a.nctrl + j] = oB0;
+        o[2 + a.nctrl + j] = oB1;
+        o[P] = oe;
+        if (g == a.M - 1) o[0] = adj ? 1.0 : sh.f[t];
       }
       // adjoints before the kick, lambda_B(g - 1) = O_g^T lambda_A(g), into the two state
       // tiles of this step; the tiles then swap roles

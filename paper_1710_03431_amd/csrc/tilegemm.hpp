@@ -43,92 +43,135 @@ template <class T> struct Vec;
 template <> struct Vec<float> { using t = float __attribute__((ext_vector_type(4))); static constexpr int W = 4; };
 template <> struct Vec<double> { using t = double __attribute__((ext_vector_type(2))); static constexpr int W = 2; };
 
-// acc[b][ct] += A[rows of tile rt][:] * B_b[:, columns of tile ct] for NB LDS operands.
-template <int NP, int NC, int LD, class T, int NB>
-__device__ __forceinline__ void panel_mma(const T* __restrict__ A, int rt, const T* const (&B)[NB],
-                                          typename Mfma<T>::acc_t (&acc)[NB][NC / 16]) {
+// Products of A with NB LDS operands over the row tiles rt = wave (mod kGW) of each wave:
+// done(i, rt, acc) takes the accumulators of its i-th row tile.  The panel comes in an even
+// number of chunks and the next one (the next row tile's first at the end) is in flight while
+// the current one is multiplied: loading a whole panel and waiting for it left the matrix
+// cores idle for more than half of a product (256 levels FP32, one 16-trajectory product:
+// 38000 cycles where the MFMAs take 16400).  With it, the wide tile copies and the sums read
+// together, the gradient of 4096 FP32 trajectories over 500 points takes 44.0 ms against 52.6.
+// The order in k is that of a plain loop.
+template <int NP, int NC, int LD, class T, int NB, class Done>
+__device__ __forceinline__ void panel_mma(const T* __restrict__ A, const T* const (&B)[NB], Done done) {
+  constexpr int RT = NP / 16, CT = NC / 16;
   constexpr int VW = Vec<T>::W;
   constexpr int NJ = NP / (4 * VW);                // vector loads per lane for the whole panel
-  // loads kept in flight: the whole FP32 panel row at 256 levels (one workgroup per CU
-  // leaves little else to hide their latency), 8 in FP64 (no gain there, more registers)
-  constexpr int JMAX = (sizeof(T) == 4) ? 16 : 8;
-  constexpr int JCH = (NJ < JMAX) ? NJ : JMAX;
+  constexpr int JCH = (NJ > 16) ? 8 : (NJ > 1 ? NJ / 2 : 1);
+  constexpr int NCH = NJ / JCH, NBUF = NCH > 1 ? 2 : 1;
+  static_assert(NCH == 1 || NCH % 2 == 0, "buffers alternate over whole panels");
   using V = typename Vec<T>::t;
-  const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
-  const V* arow = reinterpret_cast<const V*>(A + static_cast<size_t>(rt * 16 + c) * NP) + q;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  V av[NBUF][JCH];
+  auto load = [&](int rt, int ch, V* v) {
+    const V* arow = reinterpret_cast<const V*>(A + static_cast<size_t>(rt * 16 + c) * NP) + q;
+#pragma unroll
+    for (int u = 0; u < JCH; ++u) v[u] = arow[(ch * JCH + u) * 4];
+  };
+  if (wave < RT) load(wave, 0, av[0]);
+  int i = 0;
 #pragma unroll 1
-  for (int j0 = 0; j0 < NJ; j0 += JCH) {
-    V av[JCH];
+  for (int rt = wave; rt < RT; rt += kGW, ++i) {
+    typename Mfma<T>::acc_t acc[NB][CT];
 #pragma unroll
-    for (int u = 0; u < JCH; ++u) av[u] = arow[(j0 + u) * 4];
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int u = 0; u < JCH; ++u)
+      for (int ct = 0; ct < CT; ++ct) acc[b][ct] = Mfma<T>::zero();
 #pragma unroll
-      for (int e = 0; e < VW; ++e) {
-        const int k = (j0 + u) * 4 * VW + q * VW + e;
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-          for (int ct = 0; ct < NC / 16; ++ct)
-            acc[b][ct] = Mfma<T>::step(av[u][e], B[b][k * LD + ct * 16 + c], acc[b][ct]);
+    for (int ch = 0; ch < NCH; ++ch) {
+      const V* cur = av[ch % NBUF];
+      if (NBUF == 2) {
+        const bool last = ch + 1 == NCH;
+        load(last ? (rt + kGW < RT ? rt + kGW : rt) : rt, last ? 0 : ch + 1, av[(ch + 1) % NBUF]);
+        __builtin_amdgcn_sched_barrier(0);   // (else the loads sink to the products that use them)
       }
+#pragma unroll
+      for (int u = 0; u < JCH; ++u)
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+          const int k = (ch * JCH + u) * 4 * VW + q * VW + e;
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+              acc[b][ct] = Mfma<T>::step(cur[u][e], B[b][k * LD + ct * 16 + c], acc[b][ct]);
+        }
+    }
+    if (NBUF == 1 && rt + kGW < RT) load(rt + kGW, 0, av[0]);
+    done(i, rt, acc);
   }
 }
 
 // Y = (I + A) B over NP x NC (A = O_g - I or its transpose); B and Y in LDS, Y != B.
 template <int NP, int NC, int LD, class T>
 __device__ void gemm_kick(const T* __restrict__ A, const T* B, T* Y) {
-  constexpr int RT = NP / 16, CT = NC / 16;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15;
+  const int lane = threadIdx.x & 63, c = lane & 15;
   const T* const Bs[1] = {B};
-  for (int rt = wave; rt < RT; rt += kGW) {
-    typename Mfma<T>::acc_t acc[1][CT];
+  panel_mma<NP, NC, LD, T, 1>(A, Bs, [&](int, int rt, const typename Mfma<T>::acc_t (&acc)[1][NC / 16]) {
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[0][ct] = Mfma<T>::zero();
-    panel_mma<NP, NC, LD, T, 1>(A, rt, Bs, acc);
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
+    for (int ct = 0; ct < NC / 16; ++ct)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = rt * 16 + Mfma<T>::row(lane, e), col = ct * 16 + c;
         Y[r * LD + col] = acc[0][ct][e] + B[r * LD + col];
       }
-  }
+  });
 }
 
 // Y1 = (I + A) B1 and Y2 = (I + A) B2 with one pass over A (the panel loads are shared);
 // each product is accumulated in the same order as gemm_kick's.
 template <int NP, int NC, int LD, class T>
 __device__ void gemm_kick2(const T* __restrict__ A, const T* B1, T* Y1, const T* B2, T* Y2) {
-  constexpr int RT = NP / 16, CT = NC / 16;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15;
+  const int lane = threadIdx.x & 63, c = lane & 15;
   const T* const Bs[2] = {B1, B2};
-  for (int rt = wave; rt < RT; rt += kGW) {
-    typename Mfma<T>::acc_t acc[2][CT];
+  panel_mma<NP, NC, LD, T, 2>(A, Bs, [&](int, int rt, const typename Mfma<T>::acc_t (&acc)[2][NC / 16]) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc[b][ct] = Mfma<T>::zero();
-    panel_mma<NP, NC, LD, T, 2>(A, rt, Bs, acc);
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
+    for (int ct = 0; ct < NC / 16; ++ct)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = rt * 16 + Mfma<T>::row(lane, e), col = ct * 16 + c;
         Y1[r * LD + col] = acc[0][ct][e] + B1[r * LD + col];
         Y2[r * LD + col] = acc[1][ct][e] + B2[r * LD + col];
       }
-  }
+  });
 }
 
-// Copies between an LDS state tile (leading dimension LD) and a dense [NP][NC] block.
+// Copies between an LDS state tile (leading dimension LD) and a dense [NP][NC] block, 16
+// bytes at a time in global memory, all of a thread's loads in flight at once (one value at
+// a time took 18500 cycles of a 256-level step for 32 KB).
 template <int NP, int NC, int LD, class T>
 __device__ void tile_store(const T* src, T* __restrict__ dst) {
-  for (int f = threadIdx.x; f < NP * NC; f += kGThreads) dst[f] = src[(f / NC) * LD + (f % NC)];
+  using V = typename Vec<T>::t;
+  constexpr int W = Vec<T>::W, N = NP * NC / W;
+#pragma unroll
+  for (int i = 0; i < (N + kGThreads - 1) / kGThreads; ++i) {
+    const int f = threadIdx.x + i * kGThreads;
+    if (N % kGThreads && f >= N) continue;
+    const T* s = src + (f * W / NC) * LD + f * W % NC;
+    V v;
+#pragma unroll
+    for (int e = 0; e < W; ++e) v[e] = s[e];
+    reinterpret_cast<V*>(dst)[f] = v;
+  }
 }
 template <int NP, int NC, int LD, class T>
 __device__ void tile_load(const T* __restrict__ src, T* dst) {
-  for (int f = threadIdx.x; f < NP * NC; f += kGThreads) dst[(f / NC) * LD + (f % NC)] = src[f];
+  using V = typename Vec<T>::t;
+  constexpr int W = Vec<T>::W, N = NP * NC / W, I = (N + kGThreads - 1) / kGThreads;
+  V v[I];
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const int f = threadIdx.x + i * kGThreads;
+    v[i] = V{};
+    if (N % kGThreads == 0 || f < N) v[i] = reinterpret_cast<const V*>(src)[f];
+  }
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+    const int f = threadIdx.x + i * kGThreads;
+    if (N % kGThreads && f >= N) continue;
+    T* d = dst + (f * W / NC) * LD + f * W % NC;
+#pragma unroll
+    for (int e = 0; e < W; ++e) d[e] = v[i][e];
+  }
 }
 
 }  // namespace tile
