@@ -77,6 +77,7 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 struct StepArgs {
   int M, n, nq;
   int M_run;             // grid points processed (M, or fewer when autotuning)
+  int width;             // trajectories of a one-wavefront tile if fewer than 8 TQ (else 0)
   int NP, TQ;            // padded levels and column tiles of this instance (batched runs)
   int64_t tiles;         // workgroup tiles of this instance
   int64_t t_base;        // first trajectory of this launch and its first row of `partial`
@@ -1400,10 +1401,11 @@ __device__ void run_wave(CArgs& a, int64_t tile, WaveShared<NP, TQ, Mode>& sh) {
   constexpr int SEG = seg_width<NP>(), NSEG = kWave / SEG, PL = NP / SEG;
   static_assert(TT <= kWave, "one lane per trajectory");
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t tb = a.t_base + tile * TT;
+  const int width = a.width ? a.width : TT;
+  const int64_t tb = a.t_base + tile * width;
   const int lc = lane & 15;
   const int part = (lane >> 3) & 1;
-  const bool valid = lane < TT && tb + lane < a.K;
+  const bool valid = lane < width && tb + lane < a.K;
   const int tl = lane < TT ? lane : 0;   // this lane's trajectory in the LDS arrays
   const RngCache rc{sh.rng, sh.rngb, nullptr, nullptr};
 
@@ -1690,7 +1692,7 @@ __device__ void run_wave(CArgs& a, int64_t tile, WaveShared<NP, TQ, Mode>& sh) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int x = rt * 16 + Mode::row(lane, i);
-          if (j < a.K && x < a.n) a.final_state[(j * a.n + x) * 2 + part] = static_cast<double>(acc[q][rt][i]);
+          if (8 * q + (lane & 7) < width && j < a.K && x < a.n) a.final_state[(j * a.n + x) * 2 + part] = static_cast<double>(acc[q][rt][i]);
         }
     }
   }
@@ -1893,6 +1895,7 @@ struct TilePlan {
   int n = 0;
   int tq[8];
   int64_t wgs[8];
+  int width = 0;   // StepArgs::width of its tiles
   int64_t tiles() const {
     int64_t t = 0;
     for (int i = 0; i < n; ++i) t += wgs[i];
@@ -1914,7 +1917,8 @@ int explicit_tq(int NP, int precision, int tile) {
 }
 
 // Split of K trajectories over the chip.  One-wavefront tiles: 8 trajectories while the
-// launch fits the chip at once (two wavefronts per SIMD), else 16 (32 levels FP32, us a step:
+// launch fits the chip at once (two wavefronts per SIMD), else 16; 4 of the 8 columns while that
+// fits, so that all crossings of a step are handled in one pass of four lane segments (32 levels FP32, us a step:
 // 16000 trajectories 4.3 with 8, 5.1 with 16, 8.1 with 32; 10^5: 24.7, 18.5, 19.4 and 19.9
 // with 64).  At 64 levels several workgroups share a CU: one launch with the widest tile
 // that still gives every CU a workgroup.  Above, a CU holds
@@ -1931,6 +1935,11 @@ TilePlan plan_tiles(int NP, int precision, int64_t K, int cus) {
   const bool f64 = precision == AQT_FP64;
   TilePlan plan;
   if (NP <= kWaveLevels) {
+    if (cols <= 4 * static_cast<int64_t>(cus)) {
+      plan.width = 4;
+      plan.add(1, (K + 3) / 4);
+      return plan;
+    }
     const int w = cols <= 8 * static_cast<int64_t>(cus) ? 1 : 2;
     plan.add(w, (cols + w - 1) / w);
     return plan;
@@ -2039,10 +2048,11 @@ aqt_status enqueue_run(aqt_ctx* ctx, const aqt_run_params* p, const aqt_outputs*
   hipError_t e = hipSuccess;
   for (int i = 0; i < plan.n && e == hipSuccess; ++i) {
     a.TQ = plan.tq[i];
+    a.width = plan.width;
     if (prec == AQT_FP64) e = launch_mode<ModeF64>(ctx->NP, a.TQ, a, plan.wgs[i], ctx->stream);
     else if (prec == AQT_FP32) e = launch_mode<ModeF32>(ctx->NP, a.TQ, a, plan.wgs[i], ctx->stream);
     else e = launch_mode<ModeBF16>(ctx->NP, a.TQ, a, plan.wgs[i], ctx->stream);
-    a.t_base += 8 * a.TQ * plan.wgs[i];
+    a.t_base += (plan.width ? plan.width : 8 * a.TQ) * plan.wgs[i];
     a.tile0 += plan.wgs[i];
   }
   if (e != hipSuccess) return ctx->fail(AQT_EHIP, std::string("trajectory kernel launch: ") + hipGetErrorString(e));
@@ -2506,7 +2516,14 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
     aqt_status s = autotune(b);
     if (s != AQT_OK) return bail(s);
   }
+  int64_t wave_cols = 0;   // 8-trajectory columns of the instances that take one-wavefront tiles
+  for (int i = 0; i < n; ++i)
+    if (b->hargs[i].NP <= kWaveLevels) wave_cols += (b->hargs[i].K + 7) / 8;
   for (int i = 0; i < n; ++i) {
+    // as in plan_tiles (22 instances of 412 trajectories, 444 points, BF16: 8.3 ms with tuned
+    // widths, 6.5 with 4)
+    const bool narrow = !params[i].tile && b->hargs[i].NP <= kWaveLevels && wave_cols <= 4 * static_cast<int64_t>(cus);
+    if (narrow) b->tiles_per_inst[i] = 8;
     if (b->tiles_per_inst[i] == 0) {
       // heuristic: the largest allowed tile that still gives every CU several items
       int best = 1;
@@ -2516,7 +2533,8 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
     }
     StepArgs& a = b->hargs[i];
     a.TQ = b->tiles_per_inst[i] / 8;
-    a.tiles = (a.K + 8 * a.TQ - 1) / (8 * a.TQ);
+    a.width = narrow ? 4 : 0;
+    a.tiles = narrow ? (a.K + 3) / 4 : (a.K + 8 * a.TQ - 1) / (8 * a.TQ);
     aqt_ctx* c = ctxs[i];
     const size_t need = static_cast<size_t>(a.tiles) * a.M * 2 * sizeof(double);
     if (c->partial.reserve(need) != hipSuccess) return bail(b->fail(AQT_ENOMEM, "workspace allocation failed"));
