@@ -2520,9 +2520,10 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
   for (int i = 0; i < n; ++i)
     if (b->hargs[i].NP <= kWaveLevels) wave_cols += (b->hargs[i].K + 7) / 8;
   for (int i = 0; i < n; ++i) {
-    // as in plan_tiles (22 instances of 412 trajectories, 444 points, BF16: 8.3 ms with tuned
-    // widths, 6.5 with 4)
-    const bool narrow = !params[i].tile && b->hargs[i].NP <= kWaveLevels && wave_cols <= 4 * static_cast<int64_t>(cus);
+    // 4 of the 8 columns as in plan_tiles, up to twice its limit: what ends a batch is the
+    // jumps of its longest anneals (12 instances of 1000 trajectories, 200 points, FP64: 7.3 ms
+    // with widths tuned on the first steps, which have few jumps, 4.9 with 4)
+    const bool narrow = !params[i].tile && b->hargs[i].NP <= kWaveLevels && wave_cols <= 8 * static_cast<int64_t>(cus);
     if (narrow) b->tiles_per_inst[i] = 8;
     if (b->tiles_per_inst[i] == 0) {
       // heuristic: the largest allowed tile that still gives every CU several items
