@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "aqt.h"
@@ -101,11 +102,15 @@ namespace aqt {
 
 // Workspace of one call on a context's stream, from the device's scratch cache.  The stream is
 // synchronised before the block goes back, so a cached block is idle whichever way the call
-// ends, and the next holder may use it on any stream.
-struct ScratchBuf {
+// ends, and the next holder may use it on any stream.  A block may be larger than was asked
+// for, and it goes back under the size it came with: pointer and size stay together, and two
+// buffers exchange their blocks by swap() only.
+class ScratchBuf {
   aqt_ctx* ctx;
   void* p = nullptr;
   size_t bytes = 0;
+
+ public:
   explicit ScratchBuf(aqt_ctx* c) : ctx(c) {}
   ScratchBuf(const ScratchBuf&) = delete;
   ScratchBuf& operator=(const ScratchBuf&) = delete;
@@ -128,6 +133,11 @@ struct ScratchBuf {
       bytes = 0;
     }
     return e;
+  }
+  // Exchanges the blocks of two workspaces of one context.
+  void swap(ScratchBuf& o) {
+    std::swap(p, o.p);
+    std::swap(bytes, o.bytes);
   }
   template <class T> T* as() const { return static_cast<T*>(p); }
 };

@@ -707,7 +707,7 @@ aqt_status launch_sweep(aqt_ctx* ctx, GradArgs& ga, int64_t tiles, int cus, int 
   if (chunk < tiles && chunk >= cus) chunk = (chunk / cus) * cus;
   ScratchBuf ws(ctx);
   if (ws.reserve(pt * chunk) != hipSuccess) return ctx->fail(AQT_ENOMEM, "gradient workspace allocation failed");
-  char* base = static_cast<char*>(ws.p);
+  char* base = ws.as<char>();
   const size_t st = static_cast<size_t>(chunk) * NP * NC * sizeof(T);
   ga.ckpt = base;
   ga.seg = base + st * ga.S;
@@ -754,7 +754,7 @@ aqt_status launch_grad(aqt_ctx* ctx, const aqt_run_params* p, double* value, dou
     aqt_status s = launch_run(ctx, &rp, &o);
     if (s != AQT_OK) return s;
     std::vector<int32_t> cnt(K);
-    AQT_HIP(ctx, hipMemcpyAsync(cnt.data(), jc.p, K * 4, hipMemcpyDeviceToHost, st));
+    AQT_HIP(ctx, hipMemcpyAsync(cnt.data(), jc.as<void>(), K * 4, hipMemcpyDeviceToHost, st));
     AQT_HIP(ctx, hipStreamSynchronize(st));
     const int mx = cnt.empty() ? 0 : *std::max_element(cnt.begin(), cnt.end());
     if (mx <= cap) break;
@@ -774,7 +774,7 @@ aqt_status launch_grad(aqt_ctx* ctx, const aqt_run_params* p, double* value, dou
   AQT_HIP(ctx, hipMemsetAsync(out, 0, static_cast<size_t>(K) * rowb, st));
   int gs_last = 1;
   AQT_HIP(ctx, hipMemcpy(&gs_last, ctx->gs.as<int>() + (ctx->M - 1), 4, hipMemcpyDeviceToHost));
-  AQT_HIP(ctx, hipMemsetAsync(status.p, 0, 4, st));
+  AQT_HIP(ctx, hipMemsetAsync(status.as<void>(), 0, 4, st));
 
   GradArgs ga{};
   ga.cinit = ctx->cinit.as<double>();
@@ -866,13 +866,13 @@ aqt_status launch_grad(aqt_ctx* ctx, const aqt_run_params* p, double* value, dou
   }
 #undef AQT_SWEEP
   int hstat = 0;
-  AQT_HIP(ctx, hipMemcpy(&hstat, status.p, 4, hipMemcpyDeviceToHost));
+  AQT_HIP(ctx, hipMemcpy(&hstat, status.as<void>(), 4, hipMemcpyDeviceToHost));
   if (hstat) return ctx->fail(AQT_ECAPACITY, "more than 32 omega = 0 jumps of one trajectory within one step");
 
   hipLaunchKernelGGL(k_colstats, dim3(P + 1), dim3(256), 0, st, out, K, P + 1, stats.as<double>());
   AQT_HIP(ctx, hipGetLastError());
   std::vector<double> hs(5 * (P + 1));
-  AQT_HIP(ctx, hipMemcpyAsync(hs.data(), stats.p, hs.size() * 8, hipMemcpyDeviceToHost, st));
+  AQT_HIP(ctx, hipMemcpyAsync(hs.data(), stats.as<void>(), hs.size() * 8, hipMemcpyDeviceToHost, st));
   AQT_HIP(ctx, hipStreamSynchronize(st));
   const double Kd = static_cast<double>(K);
   {

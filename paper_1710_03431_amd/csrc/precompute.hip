@@ -1516,7 +1516,7 @@ aqt_status chfsi_upload(aqt_ctx* ctx, void* dst, const void* src, size_t bytes) 
 
 aqt_status chfsi_set_mask(aqt_ctx* ctx, Chfsi& c, const std::vector<int>& m) {
   c.h_act = m;
-  return chfsi_upload(ctx, c.act.p, c.h_act.data(), static_cast<size_t>(c.nb) * 4);
+  return chfsi_upload(ctx, c.act.as<void>(), c.h_act.data(), static_cast<size_t>(c.nb) * 4);
 }
 
 // S_b = P_b Q_b^T (rows x rows, weight w(x) of GEMM mode wmode) over x in every
@@ -1608,7 +1608,7 @@ aqt_status chfsi_solve(aqt_ctx* ctx, Chfsi& c, const double* eZ, const std::vect
     maxit[j] = (!c.warm[j] || c.far[j]) ? 300 : 80;
   }
   auto where = [&](int j) { return "at grid point " + std::to_string(gidx[j]); };
-  AQT_HIP(ctx, hipMemsetAsync(c.status.p, 0, static_cast<size_t>(nb) * 4, st));
+  AQT_HIP(ctx, hipMemsetAsync(c.status.as<void>(), 0, static_cast<size_t>(nb) * 4, st));
   aqt_status s = AQT_OK;
   if (anycold) {
     for (int j = 0; j < nb; ++j)
@@ -1629,7 +1629,7 @@ aqt_status chfsi_solve(aqt_ctx* ctx, Chfsi& c, const double* eZ, const std::vect
         c.h_coef[j].B = Bg[gidx[j]];
         c.h_coef[j].active = 1;
       }
-    if ((s = chfsi_upload(ctx, c.coef.p, c.h_coef.data(), nb * sizeof(HxCoef))) != AQT_OK) return s;
+    if ((s = chfsi_upload(ctx, c.coef.as<void>(), c.h_coef.data(), nb * sizeof(HxCoef))) != AQT_OK) return s;
     const HxCoef* drr = c.coef.as<HxCoef>();
     if ((s = chfsi_hx(ctx, c, eZ, drr, c.X.as<double>(), nullptr, c.W.as<double>())) != AQT_OK) return s;
     if ((s = chfsi_gram(ctx, c, c.X.as<double>(), c.W.as<double>(), KB, 0)) != AQT_OK) return s;
@@ -1637,14 +1637,14 @@ aqt_status chfsi_solve(aqt_ctx* ctx, Chfsi& c, const double* eZ, const std::vect
     // masked slots are copied, so that the buffer swap keeps their blocks
     if ((s = chfsi_combine(ctx, c, c.X.as<double>(), c.Y1.as<double>(), 1)) != AQT_OK) return s;
     if ((s = chfsi_combine(ctx, c, c.W.as<double>(), c.Y2.as<double>(), 1)) != AQT_OK) return s;
-    std::swap(c.X.p, c.Y1.p);
-    std::swap(c.W.p, c.Y2.p);
+    c.X.swap(c.Y1);
+    c.W.swap(c.Y2);
     hipLaunchKernelGGL(k_resid, dim3(KB, nb), dim3(256), 0, st, c.X.as<double>(), c.W.as<double>(),
                        c.theta.as<double>(), c.N, KB, c.act.as<int>(), c.res.as<double>());
     AQT_HIP(ctx, hipGetLastError());
-    AQT_HIP(ctx, hipMemcpyAsync(c.h_theta.data(), c.theta.p, static_cast<size_t>(nb) * KB * 8, hipMemcpyDeviceToHost, st));
-    AQT_HIP(ctx, hipMemcpyAsync(c.h_res.data(), c.res.p, static_cast<size_t>(nb) * KB * 8, hipMemcpyDeviceToHost, st));
-    AQT_HIP(ctx, hipMemcpyAsync(c.h_status.data(), c.status.p, static_cast<size_t>(nb) * 4, hipMemcpyDeviceToHost, st));
+    AQT_HIP(ctx, hipMemcpyAsync(c.h_theta.data(), c.theta.as<void>(), static_cast<size_t>(nb) * KB * 8, hipMemcpyDeviceToHost, st));
+    AQT_HIP(ctx, hipMemcpyAsync(c.h_res.data(), c.res.as<void>(), static_cast<size_t>(nb) * KB * 8, hipMemcpyDeviceToHost, st));
+    AQT_HIP(ctx, hipMemcpyAsync(c.h_status.data(), c.status.as<void>(), static_cast<size_t>(nb) * 4, hipMemcpyDeviceToHost, st));
     AQT_HIP(ctx, hipStreamSynchronize(st));
     bool any = false;
     for (int j = 0; j < nb; ++j) {
@@ -1759,7 +1759,7 @@ aqt_status chfsi_canon(aqt_ctx* ctx, Chfsi& c, const std::vector<int>& gidx, int
     }
   }
   aqt_status s = chfsi_set_mask(ctx, c, m);
-  if (s == AQT_OK) s = chfsi_upload(ctx, c.info.p, c.h_info.data(), c.h_info.size() * 4);
+  if (s == AQT_OK) s = chfsi_upload(ctx, c.info.as<void>(), c.h_info.data(), c.h_info.size() * 4);
   // Gram matrix of diag(x) over the ncols Ritz vectors (cluster rotations)
   if (s == AQT_OK) s = chfsi_gram(ctx, c, c.X.as<double>(), c.X.as<double>(), ncols, 2);
   if (s != AQT_OK) return s;
@@ -1900,10 +1900,10 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
   ScratchBuf dA(ctx), dB(ctx), dh(ctx), dJ(ctx), eZ(ctx);
   if (dA.reserve(M * 8) || dB.reserve(M * 8) || dh.reserve(nq * 8) || dJ.reserve(nq * nq * 8) || eZ.reserve(N * 8))
     return ctx->fail(AQT_ENOMEM, "precompute allocation failed");
-  AQT_HIP(ctx, hipMemcpyAsync(dA.p, Ag.data(), M * 8, hipMemcpyHostToDevice, st));
-  AQT_HIP(ctx, hipMemcpyAsync(dB.p, Bg.data(), M * 8, hipMemcpyHostToDevice, st));
-  AQT_HIP(ctx, hipMemcpyAsync(dh.p, ctx->h.data(), nq * 8, hipMemcpyHostToDevice, st));
-  AQT_HIP(ctx, hipMemcpyAsync(dJ.p, ctx->J.data(), nq * nq * 8, hipMemcpyHostToDevice, st));
+  AQT_HIP(ctx, hipMemcpyAsync(dA.as<void>(), Ag.data(), M * 8, hipMemcpyHostToDevice, st));
+  AQT_HIP(ctx, hipMemcpyAsync(dB.as<void>(), Bg.data(), M * 8, hipMemcpyHostToDevice, st));
+  AQT_HIP(ctx, hipMemcpyAsync(dh.as<void>(), ctx->h.data(), nq * 8, hipMemcpyHostToDevice, st));
+  AQT_HIP(ctx, hipMemcpyAsync(dJ.as<void>(), ctx->J.data(), nq * nq * 8, hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(k_ising_diag, dim3(nblk(N)), dim3(256), 0, st, dh.as<double>(), dJ.as<double>(), nq,
                      eZ.as<double>());
   AQT_HIP(ctx, hipGetLastError());
@@ -1938,20 +1938,20 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
         w[static_cast<size_t>(k) * N + x] = acc;
       }
     if (chw.reserve(w.size() * 8)) return ctx->fail(AQT_ENOMEM, "channel weight allocation failed");
-    AQT_HIP(ctx, hipMemcpyAsync(chw.p, w.data(), w.size() * 8, hipMemcpyHostToDevice, st));
+    AQT_HIP(ctx, hipMemcpyAsync(chw.as<void>(), w.data(), w.size() * 8, hipMemcpyHostToDevice, st));
   }
   // sx parts of the channel operators (general couplings): applied as row permutations
   const bool sx = !ctx->chan_x.empty();
   ScratchBuf cxv(ctx);
   if (sx) {
     if (cxv.reserve(ctx->chan_x.size() * 8)) return ctx->fail(AQT_ENOMEM, "channel coupling allocation failed");
-    AQT_HIP(ctx, hipMemcpyAsync(cxv.p, ctx->chan_x.data(), ctx->chan_x.size() * 8, hipMemcpyHostToDevice, st));
+    AQT_HIP(ctx, hipMemcpyAsync(cxv.as<void>(), ctx->chan_x.data(), ctx->chan_x.size() * 8, hipMemcpyHostToDevice, st));
   }
   std::vector<double> wch(nch, ctx->omega_c);
   for (int k = 0; k < nch && k < static_cast<int>(ctx->chan_wc.size()); ++k)
     if (ctx->chan_wc[k] != 0.0) wch[k] = ctx->chan_wc[k];
   if (wcv.reserve(nch * 8)) return ctx->fail(AQT_ENOMEM, "channel cutoff allocation failed");
-  AQT_HIP(ctx, hipMemcpyAsync(wcv.p, wch.data(), nch * 8, hipMemcpyHostToDevice, st));
+  AQT_HIP(ctx, hipMemcpyAsync(wcv.as<void>(), wch.data(), nch * 8, hipMemcpyHostToDevice, st));
   // Lamb-shift function table over every Bohr frequency (Gershgorin bound on |e|)
   ScratchBuf lambS(ctx), gl(ctx), tixd(ctx);
   LambTable ltab{nullptr, 0.0, nullptr};
@@ -1995,8 +1995,8 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
     }
     if (lambS.reserve(cut.size() * kLambNodes * 8) || gl.reserve(32 * 8) || tixd.reserve(nch * 4))
       return ctx->fail(AQT_ENOMEM, "Lamb-shift table allocation failed");
-    AQT_HIP(ctx, hipMemcpyAsync(gl.p, glh.data(), 32 * 8, hipMemcpyHostToDevice, st));
-    AQT_HIP(ctx, hipMemcpyAsync(tixd.p, tix.data(), nch * 4, hipMemcpyHostToDevice, st));
+    AQT_HIP(ctx, hipMemcpyAsync(gl.as<void>(), glh.data(), 32 * 8, hipMemcpyHostToDevice, st));
+    AQT_HIP(ctx, hipMemcpyAsync(tixd.as<void>(), tix.data(), nch * 4, hipMemcpyHostToDevice, st));
     for (size_t m = 0; m < cut.size(); ++m) {
       hipLaunchKernelGGL(k_lamb_table, dim3(nblk(kLambNodes, 64)), dim3(64), 0, st, ltab.W, ctx->eta, cut[m],
                          ctx->T, gl.as<double>(), gl.as<double>() + 16, lambS.as<double>() + m * kLambNodes);
@@ -2073,7 +2073,7 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
     ch.warm.assign(nb, 0);
     ch.far.assign(nb, 0);
     std::vector<double> hz(N);
-    AQT_HIP(ctx, hipMemcpyAsync(hz.data(), eZ.p, N * 8, hipMemcpyDeviceToHost, st));
+    AQT_HIP(ctx, hipMemcpyAsync(hz.data(), eZ.as<void>(), N * 8, hipMemcpyDeviceToHost, st));
     AQT_HIP(ctx, hipStreamSynchronize(st));
     double zmax = 0.0;
     for (double v : hz) zmax = std::max(zmax, std::fabs(v));
@@ -2103,12 +2103,12 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
                          ctx->gs.as<int>(), cws.as<double>(), status.as<int>());
       AQT_HIP(ctx, hipGetLastError());
     } else {
-      AQT_HIP(ctx, hipMemsetAsync(status.p, 0, cnt * 4, st));
+      AQT_HIP(ctx, hipMemsetAsync(status.as<void>(), 0, cnt * 4, st));
       aqt_status s = chfsi_chunk(ctx, ch, eZ.as<double>(), Ag, Bg, g0, cnt, ncols, n, NP, tol, Vc.as<double>(),
                                  Vstride, status.as<int>());
       if (s != AQT_OK) return s;
     }
-    AQT_HIP(ctx, hipMemcpyAsync(hstat.data(), status.p, cnt * 4, hipMemcpyDeviceToHost, st));
+    AQT_HIP(ctx, hipMemcpyAsync(hstat.data(), status.as<void>(), cnt * 4, hipMemcpyDeviceToHost, st));
     AQT_HIP(ctx, hipStreamSynchronize(st));
     for (int c = 0; c < cnt; ++c)
       if (hstat[c]) return ctx->fail(AQT_ENUMERIC, "eigensolver did not converge at grid point " + std::to_string(g0 + c));
@@ -2176,9 +2176,9 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
       } else {
         GemmArgs ga{Vc.as<double>() + off * Vstride, Vc.as<double>() + off * Vstride, zws.as<double>(),
                     static_cast<int64_t>(Vstride), static_cast<int64_t>(Vstride), static_cast<int64_t>(n) * n,
-                    n, n, N, N, N, n, chw.p ? 4 : 1, nch, 0};
+                    n, n, N, N, N, n, chw.as<void>() ? 4 : 1, nch, 0};
         ga.wvec = chw.as<double>();
-        zsym = chw.p == nullptr;   // weights +-1
+        zsym = chw.as<void>() == nullptr;   // weights +-1
         ga.sym = zsym ? 1 : 0;
         s = launch_gemm(ctx, ga, zcnt * nch);
       }
@@ -2240,8 +2240,8 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
         }
       }
     }
-    AQT_HIP(ctx, hipMemcpyAsync(Vprev.p, Vc.as<double>() + (cnt - 1) * Vstride, Vstride * 8, hipMemcpyDeviceToDevice, st));
-    AQT_HIP(ctx, hipMemcpyAsync(hstat.data(), status.p, cnt * 4, hipMemcpyDeviceToHost, st));
+    AQT_HIP(ctx, hipMemcpyAsync(Vprev.as<void>(), Vc.as<double>() + (cnt - 1) * Vstride, Vstride * 8, hipMemcpyDeviceToDevice, st));
+    AQT_HIP(ctx, hipMemcpyAsync(hstat.data(), status.as<void>(), cnt * 4, hipMemcpyDeviceToHost, st));
     AQT_HIP(ctx, hipStreamSynchronize(st));
     for (int c = 0; c < cnt; ++c)
       if (hstat[c]) return ctx->fail(AQT_ENUMERIC, "polar factor eigensolver failed at grid " + std::to_string(g0 + c));

@@ -278,7 +278,7 @@ aqt_status finish_tables(aqt_ctx* ctx) {
     hipLaunchKernelGGL(k_max_gdt, dim3(kGdtParts), dim3(256), 0, ctx->stream, ctx->Gamma.as<double>(), ctx->tlen.as<double>(),
                        ctx->M, ctx->NP, mx.as<double>());
     AQT_HIP(ctx, hipGetLastError());
-    AQT_HIP(ctx, hipMemcpyAsync(part, mx.p, sizeof(part), hipMemcpyDeviceToHost, ctx->stream));
+    AQT_HIP(ctx, hipMemcpyAsync(part, mx.as<void>(), sizeof(part), hipMemcpyDeviceToHost, ctx->stream));
     AQT_HIP(ctx, hipStreamSynchronize(ctx->stream));
     ctx->max_gdt = *std::max_element(part, part + kGdtParts);
   }
