@@ -291,6 +291,7 @@ aqt_status pack_for_precision(aqt_ctx* ctx, int precision) {
   if (ctx->packed_for == precision) return AQT_OK;
   const int64_t nd = static_cast<int64_t>(ctx->M) * ctx->NP * ctx->NP;
   const int64_t nv = static_cast<int64_t>(ctx->M) * ctx->NP;
+  ctx->packed_for = -1;   // until every operand is enqueued: a failure below leaves some rewritten or freed
   // buffers of another precision or of smaller tables are kept where they are large enough
   if (precision != AQT_BF16) ctx->pk_b.release();
   if (precision != AQT_FP32) ctx->pk_ch.release();

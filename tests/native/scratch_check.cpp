@@ -1,49 +1,9 @@
 // The workspace cache (csrc/scratch.hip, ScratchBuf) behind a stubbed device allocator: every
 // block's true size is known here, so a block handed out below the size asked for is an error.
-#include <cstdio>
-#include <cstdlib>
-#include <map>
 #include <random>
-#include <utility>
-#include <vector>
 
 #include "ctx.hpp"
-
-namespace {
-
-std::map<char*, size_t> g_live;   // blocks of the stubbed device memory
-char* g_next = reinterpret_cast<char*>(size_t(1) << 44);
-size_t g_used = 0, g_limit = ~size_t(0);
-
-#define CHECK(cond)                                                     \
-  do {                                                                  \
-    if (!(cond)) {                                                      \
-      std::printf("%s:%d: %s\n", __FILE__, __LINE__, #cond);            \
-      std::exit(1);                                                     \
-    }                                                                   \
-  } while (0)
-
-}  // namespace
-
-extern "C" {
-hipError_t hipMalloc(void** p, size_t n) {
-  if (n > g_limit - g_used) return hipErrorOutOfMemory;
-  g_live[g_next] = n;
-  *p = g_next;
-  g_next += (n + 4095) & ~size_t(4095);
-  g_used += n;
-  return hipSuccess;
-}
-hipError_t hipFree(void* p) {
-  const auto it = g_live.find(static_cast<char*>(p));
-  CHECK(it != g_live.end());
-  g_used -= it->second;
-  g_live.erase(it);
-  return hipSuccess;
-}
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
-}
+#include "hip_stub.hpp"
 
 namespace {
 
@@ -51,7 +11,7 @@ using aqt::ScratchBuf;
 
 void take(ScratchBuf& b, size_t n) {
   CHECK(b.reserve(n) == hipSuccess);
-  CHECK(g_live.at(b.as<char>()) >= n);
+  CHECK(stub::live.at(b.as<char>()) >= n);
 }
 
 // Requests of the iterative eigensolver with n-state blocks, 32 levels: four blocks, the
@@ -68,7 +28,7 @@ void iterative(aqt_ctx* ctx, size_t N, size_t KB, size_t slots, int swaps) {
   for (int k = 0; k < swaps; ++k) {
     X.swap(Y1);
     W.swap(Y2);
-    for (ScratchBuf* b : {&X, &Y1, &Y2, &W}) CHECK(g_live.at(b->as<char>()) >= blk);
+    for (ScratchBuf* b : {&X, &Y1, &Y2, &W}) CHECK(stub::live.at(b->as<char>()) >= blk);
   }
 }
 
@@ -86,7 +46,7 @@ void mixed_sizes() {
       take(other, 1 + rng() % (size_t(1) << 30));
     }
     aqt::scratch_context(0, -1);
-    CHECK(g_live.empty());   // the last context gives everything back
+    CHECK(stub::live.empty());   // the last context gives everything back
   }
 }
 

@@ -1,7 +1,10 @@
-"""Host-side parts of the library compiled for the CPU alone, with the device calls stubbed."""
+"""The library's host code compiled for the CPU alone and linked against a HIP runtime without a
+device (tests/native/hip_stub.cpp), which records launches and waits and can run out of memory."""
 import os
+import re
 import shutil
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -10,23 +13,43 @@ CSRC = os.path.join(ROOT, "paper_1710_03431_amd", "csrc")
 NATIVE = os.path.join(ROOT, "tests", "native")
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
 
-
-def run_native(tmp_path, check, *sources):
-    """Compile the check and the library's sources without device code, link them without the
-    HIP runtime (the check supplies the calls they make) and run."""
-    objs = []
-    for src in [os.path.join(NATIVE, check)] + [os.path.join(CSRC, s) for s in sources]:
-        obj = str(tmp_path / (os.path.basename(src) + ".o"))
-        subprocess.run([HIPCC, "--offload-host-only", "-x", "hip", "--offload-arch=gfx950", "-O1", "-fPIC", "-std=c++17",
-                        "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-c", src, "-o", obj], check=True)
-        objs.append(obj)
-    exe = str(tmp_path / "check")
-    subprocess.run(["g++", *objs, "-o", exe, "-lpthread"], check=True)
-    return subprocess.run([exe], capture_output=True, text=True)
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
-def test_workspace_cache_never_hands_out_a_smaller_block(tmp_path):
-    """Mixed sizes and both parities of the block solver's buffer exchange."""
-    res = run_native(tmp_path, "scratch_check.cpp", "scratch.hip")
+def compile_host(src, out):
+    obj = os.path.join(out, os.path.basename(src) + ".o")
+    subprocess.run([HIPCC, "--offload-host-only", "-x", "hip", "--offload-arch=gfx950", "-O1", "-fPIC", "-std=c++17",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-I" + NATIVE, "-c", src, "-o", obj],
+                   check=True)
+    return obj
+
+
+@pytest.fixture(scope="module")
+def library(tmp_path_factory):
+    """Host objects of every source and of the stub."""
+    out = str(tmp_path_factory.mktemp("host"))
+    srcs = [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith(".hip")]
+    with ThreadPoolExecutor(max_workers=4) as ex:
+        objs = list(ex.map(lambda s: compile_host(s, out), srcs + [os.path.join(NATIVE, "hip_stub.cpp")]))
+    nm = subprocess.run(["nm", "-u", *objs], capture_output=True, text=True, check=True).stdout
+    fat = sorted(set(re.findall(r"__hip_fatbin_\w+", nm)))   # device code left out
+    return out, objs, ["-Wl,--defsym=%s=0" % f for f in fat]
+
+
+def run_check(library, name):
+    out, objs, syms = library
+    exe = os.path.join(out, name + ".exe")
+    obj = compile_host(os.path.join(NATIVE, name + ".cpp"), out)
+    subprocess.run(["g++", "-no-pie", obj, *objs, *syms, "-o", exe, "-lpthread"], check=True)
+    res = subprocess.run([exe], capture_output=True, text=True)
     assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_workspace_cache_never_hands_out_a_smaller_block(library):
+    """Mixed sizes and both parities of the block solver's buffer exchange."""
+    run_check(library, "scratch_check")
+
+
+def test_operands_of_a_failed_packing_are_not_resident(library):
+    """Every allocation of a change of precision failing in turn."""
+    run_check(library, "pack_check")
