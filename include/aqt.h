@@ -396,7 +396,10 @@ AQT_API aqt_status aqt_grad_pgs(aqt_ctx* ctx, const aqt_run_params* params, doub
  * graph (replayed by aqt_batch_launch); AQT_BATCH_AUTOTUNE times the supported tile
  * sizes per level count on a shortened anneal and keeps the fastest (instances
  * with a non-zero params[i].tile keep theirs).  Output pointers are bound at
- * creation.  On failure *out may still receive a batch whose aqt_batch_last_error
+ * creation, and every launch reads the tables and the packed operands that the contexts
+ * hold: between creation and the last launch no member may load other tables or run in
+ * another precision (such a run waits for launches in flight, those after it are
+ * invalid).  On failure *out may still receive a batch whose aqt_batch_last_error
  * explains the failure; it must be destroyed.  Launches on the first context's
  * stream; jump_totals and net_hist accumulate across launches. */
 typedef struct aqt_batch aqt_batch;

@@ -292,7 +292,10 @@ aqt_status pack_for_precision(aqt_ctx* ctx, int precision) {
   const int64_t nd = static_cast<int64_t>(ctx->M) * ctx->NP * ctx->NP;
   const int64_t nv = static_cast<int64_t>(ctx->M) * ctx->NP;
   ctx->packed_for = -1;   // until every operand is enqueued: a failure below leaves some rewritten or freed
-  // buffers of another precision or of smaller tables are kept where they are large enough
+  // Buffers of another precision or of smaller tables are kept where they are large enough and
+  // rewritten in this stream; launches on other streams (a batch with this context) may still
+  // read them, so wait for the device as freeing them would.
+  if (ctx->pk_a.p) AQT_HIP(ctx, hipDeviceSynchronize());
   if (precision != AQT_BF16) ctx->pk_b.release();
   if (precision != AQT_FP32) ctx->pk_ch.release();
   if (precision == AQT_FP64) {

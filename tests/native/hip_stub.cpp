@@ -5,6 +5,7 @@
 namespace stub {
 std::map<char*, size_t> live;
 size_t used = 0, limit = size_t(288) << 30;
+size_t allocations = ~size_t(0);
 std::vector<Call> calls;
 std::function<void(const Call&)> on_call;
 std::function<void(void*, const void*, size_t)> on_download;
@@ -46,7 +47,8 @@ using namespace stub;
 
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
-  if (n > limit - used) return hipErrorOutOfMemory;
+  if (n > limit - used || !allocations) return hipErrorOutOfMemory;
+  --allocations;
   live[next_block] = n;
   *p = next_block;
   next_block += (n + 4096) & ~size_t(4095);

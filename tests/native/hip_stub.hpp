@@ -29,6 +29,7 @@ struct Call {
 };
 extern std::map<char*, size_t> live;          // allocated blocks
 extern size_t used, limit;                    // bytes, and the bytes there are
+extern size_t allocations;                    // that still succeed
 extern std::vector<Call> calls;               // in order
 extern std::function<void(const Call&)> on_call;
 extern std::function<void(void* dst, const void* src, size_t n)> on_download;

@@ -1,4 +1,4 @@
-// Packed step operands when their packing fails half way.
+// Packed step operands: a packing that fails half way, and one while other streams read them.
 #include "host_check.hpp"
 
 namespace {
@@ -18,12 +18,12 @@ void failed_packing() {
   for (int from : precisions)
     for (int to : precisions) {
       if (from == to) continue;
-      for (size_t room = 0; room < (size_t(4) << 20); room += 4096) {
-        aqt_ctx* c = context_with_tables(128, 7, 20);
+      for (size_t good = 0;; ++good) {
+        aqt_ctx* c = context_with_tables(128, 7, 3);
         CHECK(run(c, from) == AQT_OK && c->packed_for == from);
-        stub::limit = stub::used + room;
+        stub::allocations = good;
         const aqt_status s = run(c, to);
-        stub::limit = size_t(288) << 30;
+        stub::allocations = ~size_t(0);
         if (s == AQT_OK) {
           aqt_destroy(c);
           break;
@@ -37,9 +37,43 @@ void failed_packing() {
     }
 }
 
+size_t first(const char* part, size_t from = 0) {
+  size_t k = from;
+  while (k < stub::calls.size() && stub::calls[k].name.find(part) == std::string::npos) ++k;
+  return k;
+}
+
+// A batch in flight on its own stream reads the operands of a member that is then run in
+// another precision: the rewriting waits for it.
+void packing_under_a_batch() {
+  const int precisions[] = {AQT_FP64, AQT_FP32, AQT_BF16};
+  for (int from : precisions)
+    for (int to : precisions) {
+      if (from == to) continue;
+      aqt_ctx* c[2] = {context_with_tables(16, 4, 3, reinterpret_cast<hipStream_t>(16)),
+                       context_with_tables(16, 4, 3, reinterpret_cast<hipStream_t>(32))};
+      aqt_run_params p[2]{};
+      aqt_outputs o[2]{};
+      for (auto& q : p) {
+        q.precision = from;
+        q.n_traj = 64;
+      }
+      aqt_batch* b = nullptr;
+      CHECK(aqt_batch_create(&b, c, 2, p, o, 0) == AQT_OK);
+      CHECK(aqt_batch_launch(b) == AQT_OK);
+      stub::calls.clear();
+      CHECK(run(c[1], to) == AQT_OK);
+      // freeing waits for the device as well, but only some packings free a buffer
+      CHECK(first("hipDeviceSynchronize") < first("k_pack") && first("k_pack") < stub::calls.size());
+      aqt_batch_destroy(b);
+      for (aqt_ctx* k : c) aqt_destroy(k);
+    }
+}
+
 }  // namespace
 
 int main() {
   failed_packing();
+  packing_under_a_batch();
   return 0;
 }

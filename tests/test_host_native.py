@@ -50,6 +50,7 @@ def test_workspace_cache_never_hands_out_a_smaller_block(library):
     run_check(library, "scratch_check")
 
 
-def test_operands_of_a_failed_packing_are_not_resident(library):
-    """Every allocation of a change of precision failing in turn."""
+def test_packed_operands(library):
+    """Every allocation of a change of precision failing in turn; a change of precision while a
+    batch on another stream reads the operands."""
     run_check(library, "pack_check")
