@@ -2461,7 +2461,8 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
     if (s == AQT_OK) s = pack_for_precision(c, b->precision);
     if (s != AQT_OK) return bail(b->fail(s, c->err));
   }
-  if (hipStreamSynchronize(b->stream) != hipSuccess) return bail(b->fail(AQT_EHIP, "packing failed"));
+  for (int i = 0; i < n; ++i)   // packed on the members' streams, read on the first one's
+    if (hipStreamSynchronize(ctxs[i]->stream) != hipSuccess) return bail(b->fail(AQT_EHIP, "packing failed"));
   b->tiles_per_inst.assign(n, 0);
   for (int i = 0; i < n; ++i) b->tiles_per_inst[i] = params[i].tile;
   // provisional args (TQ fixed below)

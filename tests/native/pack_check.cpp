@@ -70,10 +70,43 @@ void packing_under_a_batch() {
     }
 }
 
+// The operands that a batch packs on its members' streams are complete before its own stream
+// reads them.
+void batch_waits_for_its_packings() {
+  hipStream_t st[3];
+  for (size_t k = 0; k < 3; ++k) st[k] = reinterpret_cast<hipStream_t>(16 * (k + 1));
+  aqt_ctx* c[3];
+  aqt_run_params p[3]{};
+  aqt_outputs o[3]{};
+  for (int k = 0; k < 3; ++k) {
+    c[k] = context_with_tables(16, 4, 3, st[k]);
+    p[k].precision = AQT_FP32;
+    p[k].n_traj = 64;
+  }
+  stub::calls.clear();
+  aqt_batch* b = nullptr;
+  CHECK(aqt_batch_create(&b, c, 3, p, o, AQT_BATCH_AUTOTUNE) == AQT_OK);
+  CHECK(aqt_batch_launch(b) == AQT_OK);
+  const size_t runs = first("k_batch");
+  CHECK(runs < stub::calls.size());
+  for (hipStream_t s : st) {
+    size_t packed = 0, waited = 0;
+    for (size_t k = 0; k < runs; ++k) {
+      if (stub::calls[k].stream != s) continue;
+      if (stub::calls[k].name.find("k_") != std::string::npos) packed = k;
+      if (stub::calls[k].name == "hipStreamSynchronize") waited = k;
+    }
+    CHECK(packed < waited);
+  }
+  aqt_batch_destroy(b);
+  for (aqt_ctx* k : c) aqt_destroy(k);
+}
+
 }  // namespace
 
 int main() {
   failed_packing();
   packing_under_a_batch();
+  batch_waits_for_its_packings();
   return 0;
 }
