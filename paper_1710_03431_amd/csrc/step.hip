@@ -1988,9 +1988,37 @@ TilePlan plan_tiles(int NP, int precision, int64_t K, int cus) {
   return plan;
 }
 
+// One launch of w column tiles a workgroup.
+TilePlan single_width(const aqt_run_params* p, int w) {
+  TilePlan plan;
+  plan.add(w, (p->n_traj + 8 * w - 1) / (8 * w));
+  return plan;
+}
+
+// The widest tile alone: the fewest per-tile sums.
+TilePlan widest_plan(const aqt_ctx* ctx, const aqt_run_params* p) {
+  int w = 1;
+  for (int tq : kTQ)
+    if (tq_allowed(ctx->NP, tq, p->precision == AQT_FP64)) w = tq;
+  return single_width(p, w);
+}
+
+double partial_bytes(const aqt_ctx* ctx, const TilePlan& plan) {
+  return static_cast<double>(plan.tiles()) * ctx->M * 2 * sizeof(double);
+}
+
+// Up to 32 levels the 16-trajectory tiles keep n_traj n_grid bytes of per-tile sums.  Beyond
+// this many, tiles of 32 run instead: half the sums and the same time at such sizes (32 levels,
+// 400000 trajectories, us a step with 16, 32 and 64: FP64 141, 143, 189; FP32 74, 69, 88; BF16
+// 65, 60, 79).
+constexpr double kMaxPartialBytes = 4.0 * (1u << 30);
+
 // Plan of a run (explicit or chosen width); empty for an unsupported explicit tile.
 TilePlan run_plan(const aqt_ctx* ctx, const aqt_run_params* p) {
-  if (!p->tile) return plan_tiles(ctx->NP, p->precision, p->n_traj, ctx->cus > 0 ? ctx->cus : 256);
+  if (!p->tile) {
+    const TilePlan plan = plan_tiles(ctx->NP, p->precision, p->n_traj, ctx->cus > 0 ? ctx->cus : 256);
+    return (ctx->NP <= kWaveLevels && partial_bytes(ctx, plan) > kMaxPartialBytes) ? single_width(p, 4) : plan;
+  }
   TilePlan plan;
   const int tq = explicit_tq(ctx->NP, p->precision, p->tile);
   if (tq) plan.add(tq, (p->n_traj + 8 * tq - 1) / (8 * tq));
@@ -2087,10 +2115,19 @@ aqt_status launch_run(aqt_ctx* ctx, const aqt_run_params* p, const aqt_outputs* 
   if (s != AQT_OK) return s;
   s = pack_for_precision(ctx, prec);
   if (s != AQT_OK) return s;
-  const TilePlan plan = run_plan(ctx, p);
+  TilePlan plan = run_plan(ctx, p);
   if (!plan.n) return ctx->fail(AQT_EINVAL, "unsupported tile size for this level count and precision");
-  const size_t need = static_cast<size_t>(plan.tiles()) * ctx->M * 2 * sizeof(double);
-  if (ctx->partial.reserve(need) != hipSuccess) return ctx->fail(AQT_ENOMEM, "workspace allocation failed");
+  hipError_t e = ctx->partial.reserve(static_cast<size_t>(partial_bytes(ctx, plan)));
+  for (int tq : kTQ) {   // a chosen width whose sums do not fit gives way to wider ones
+    if (e == hipSuccess || p->tile) break;
+    if (!tq_allowed(ctx->NP, tq, prec == AQT_FP64)) continue;
+    const TilePlan wider = single_width(p, tq);
+    if (wider.tiles() >= plan.tiles()) continue;
+    (void)hipGetLastError();
+    plan = wider;
+    e = ctx->partial.reserve(static_cast<size_t>(partial_bytes(ctx, plan)));
+  }
+  if (e != hipSuccess) return ctx->fail(AQT_ENOMEM, "workspace allocation failed");
   return enqueue_run(ctx, p, o, plan, ctx->partial.as<double>());
 }
 
@@ -2124,16 +2161,8 @@ aqt_status launch_run_noalloc(aqt_ctx* ctx, const aqt_run_params* p, const aqt_o
   if (!base) return ctx->fail(AQT_ESTATE, "the device scratch buffer has no address (aqt_create did not set it up)");
   TilePlan plan = run_plan(ctx, p);
   if (!plan.n) return ctx->fail(AQT_EINVAL, "unsupported tile size for this level count and precision");
-  auto bytes = [&]() { return static_cast<double>(plan.tiles()) * ctx->M * 2 * sizeof(double); };
-  if (!p->tile && bytes() > static_cast<double>(kScratchBytes)) {
-    // the widest tile needs the least scratch
-    int w = 1;
-    for (int tq : kTQ)
-      if (tq_allowed(ctx->NP, tq, prec == AQT_FP64)) w = tq;
-    plan = TilePlan();
-    plan.add(w, (p->n_traj + 8 * w - 1) / (8 * w));
-  }
-  const double need = bytes();
+  if (!p->tile && partial_bytes(ctx, plan) > static_cast<double>(kScratchBytes)) plan = widest_plan(ctx, p);
+  const double need = partial_bytes(ctx, plan);
   if (need > static_cast<double>(kScratchBytes))
     return ctx->fail(AQT_EINVAL, "the run needs " + std::to_string(static_cast<long long>(need)) +
                                      " bytes of per-tile sums (tiles x n_grid x 16), more than the " +

@@ -54,3 +54,8 @@ def test_packed_operands(library):
     """Every allocation of a change of precision failing in turn; a change of precision while a
     batch on another stream reads the operands."""
     run_check(library, "pack_check")
+
+
+def test_per_tile_sums_of_large_runs(library):
+    """Memory limits at and below what the wider tiles need; the bound beyond which they are taken."""
+    run_check(library, "plan_check")
