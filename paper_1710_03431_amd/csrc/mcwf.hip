@@ -76,6 +76,59 @@ __device__ int first_exceeding(const double (&w)[NR], double target) {
   return -1;
 }
 
+// Y = (I + A) B over NP x NC, B and Y in LDS: the product of tile::gemm_kick, in its order of k,
+// with the loads of a chunk issued and used at once.  One product a step, followed by the
+// sub-steps with their own registers, does not pay for panels in flight across row tiles: with
+// them a run of 16384 trajectories, 200 points and two sub-steps takes 17.4 ms against 16.8 at
+// 256 levels in FP32, 11.8 against 11.2 at 128 in FP64, 8.2 against 7.9 at 64 (the same at 32).
+template <int NP, int NC, int LD, class T>
+__device__ __forceinline__ void panel_plain(const T* __restrict__ A, int rt, const T* const (&B)[1],
+                                            typename Mfma<T>::acc_t (&acc)[1][NC / 16]) {
+  constexpr int VW = Vec<T>::W;
+  constexpr int NJ = NP / (4 * VW);                // vector loads per lane for the whole panel
+  // loads in flight: the whole FP32 panel row at 256 levels (one workgroup per CU leaves
+  // little else to hide their latency), 8 in FP64 (no gain there, more registers)
+  constexpr int JMAX = (sizeof(T) == 4) ? 16 : 8;
+  constexpr int JCH = (NJ < JMAX) ? NJ : JMAX;
+  using V = typename Vec<T>::t;
+  const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  const V* arow = reinterpret_cast<const V*>(A + static_cast<size_t>(rt * 16 + c) * NP) + q;
+#pragma unroll 1
+  for (int j0 = 0; j0 < NJ; j0 += JCH) {
+    V av[JCH];
+#pragma unroll
+    for (int u = 0; u < JCH; ++u) av[u] = arow[(j0 + u) * 4];
+#pragma unroll
+    for (int u = 0; u < JCH; ++u)
+#pragma unroll
+      for (int e = 0; e < VW; ++e) {
+        const int k = (j0 + u) * 4 * VW + q * VW + e;
+#pragma unroll
+        for (int ct = 0; ct < NC / 16; ++ct)
+          acc[0][ct] = Mfma<T>::step(av[u][e], B[0][k * LD + ct * 16 + c], acc[0][ct]);
+      }
+  }
+}
+template <int NP, int NC, int LD, class T>
+__device__ void kick_plain(const T* __restrict__ A, const T* B, T* Y) {
+  constexpr int RT = NP / 16, CT = NC / 16;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15;
+  const T* const Bs[1] = {B};
+  for (int rt = wave; rt < RT; rt += kGW) {
+    typename Mfma<T>::acc_t acc[1][CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[0][ct] = Mfma<T>::zero();
+    panel_plain<NP, NC, LD, T>(A, rt, Bs, acc);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = rt * 16 + Mfma<T>::row(lane, e), col = ct * 16 + c;
+        Y[r * LD + col] = acc[0][ct][e] + B[r * LD + col];
+      }
+  }
+}
+
 template <int NP, int TT, class T>
 __global__ __launch_bounds__(kGThreads) void k_fixed_step(FixArgs a) {
   constexpr int NC = 2 * TT;
@@ -105,7 +158,7 @@ __global__ __launch_bounds__(kGThreads) void k_fixed_step(FixArgs a) {
         PA[x * LD + col] = (!(col & 1) && act) ? static_cast<T>(a.cinit[x]) : static_cast<T>(0);
       }
     } else {
-      gemm_kick<NP, NC, LD, T>(static_cast<const T*>(a.pD) + static_cast<size_t>(g) * NP * NP, PB, PA);
+      kick_plain<NP, NC, LD, T>(static_cast<const T*>(a.pD) + static_cast<size_t>(g) * NP * NP, PB, PA);
     }
     __syncthreads();
     const size_t gN = static_cast<size_t>(g) * NP;

@@ -1,5 +1,5 @@
-// Tile products shared by the sweep kernels (gradient, fixed-step unraveling): a
-// workgroup of kGW wavefronts holds TT trajectories as an LDS tile [NP][LD] (columns
+// Tile products of the gradient sweep, and the operand layout that the fixed-step unraveling
+// shares: a workgroup of kGW wavefronts holds TT trajectories as an LDS tile [NP][LD] (columns
 // 2t, 2t + 1 = re, im of trajectory t) and multiplies it by NP x NP operands read from
 // global memory on MFMA (FP32 or FP64 16x16x4).
 #pragma once
