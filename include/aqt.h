@@ -394,8 +394,9 @@ AQT_API aqt_status aqt_grad_pgs(aqt_ctx* ctx, const aqt_run_params* params, doub
  * instance's observable sums.  All contexts must be on one device and use one
  * precision.  flags: AQT_BATCH_GRAPH captures the launch sequence once into a HIP
  * graph (replayed by aqt_batch_launch); AQT_BATCH_AUTOTUNE times the supported tile
- * sizes per level count on a shortened anneal and keeps the fastest (instances
- * with a non-zero params[i].tile keep theirs).  Output pointers are bound at
+ * sizes per level count above 32 on a shortened anneal and keeps the fastest; up to 32
+ * levels the size follows from the number of trajectories, with the flag or without
+ * (instances with a non-zero params[i].tile keep theirs).  Output pointers are bound at
  * creation, and every launch reads the tables and the packed operands that the contexts
  * hold: between creation and the last launch no member may load other tables or run in
  * another precision (such a run waits for launches in flight, those after it are

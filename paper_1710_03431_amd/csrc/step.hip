@@ -2352,13 +2352,26 @@ std::vector<BatchItem> build_items(const std::vector<StepArgs>& args, ClassSpans
   return out;
 }
 
-// Time each allowed tile size per level count on a shortened anneal (outputs
+// Trajectories a tile of a batch's instances up to kWaveLevels levels, from the 8-trajectory
+// columns of all of them.  A one-wavefront tile handles its crossings one pass after another, so
+// what ends a batch is the jumps of its longest anneals, and narrow tiles spread them.  4 (half
+// the columns, as in plan_tiles) up to 8 columns a CU: 12 instances of 1000 trajectories, 200
+// points, FP64 take 4.9 ms with 4 and 7.3 with 8.  8 up to 256 a CU, 16 beyond (ms with 8, 16
+// and 32; 24 instances, 24 a CU: FP64 11.3, 18.6, 32.9, FP32 7.1, 12.4, 22.4; 60 instances, 240 a
+// CU, 100 points: 58.9, 62.8, 74.6 and 34.7, 37.5, 43.7; 24 instances, 469 a CU: 74.3, 69.3, 71.6
+// and 43.4, 40.7, 44.7).  Timing the first steps, which have few jumps, picks wider tiles than
+// that (60 instances of 2048, 200 points, BF16: 27.0 ms against 14.4), so they are not timed.
+int wave_batch_tile(int64_t cols, int cus) {
+  return cols <= 8 * static_cast<int64_t>(cus) ? 4 : cols <= 256 * static_cast<int64_t>(cus) ? 8 : 16;
+}
+
+// Time each allowed tile size per level count above kWaveLevels on a shortened anneal (outputs
 // discarded) and keep the fastest per trajectory-step.
 aqt_status autotune(aqt_batch* b) {
   const int tune_steps = 24;
   std::vector<int> nps;
   for (auto& a : b->hargs)
-    if (std::find(nps.begin(), nps.end(), a.NP) == nps.end()) nps.push_back(a.NP);
+    if (a.NP > kWaveLevels && std::find(nps.begin(), nps.end(), a.NP) == nps.end()) nps.push_back(a.NP);
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
     return b->fail(AQT_EHIP, "event creation failed");
@@ -2550,25 +2563,30 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
   for (int i = 0; i < n; ++i)
     if (b->hargs[i].NP <= kWaveLevels) wave_cols += (b->hargs[i].K + 7) / 8;
   for (int i = 0; i < n; ++i) {
-    // 4 of the 8 columns as in plan_tiles, up to twice its limit: what ends a batch is the
-    // jumps of its longest anneals (12 instances of 1000 trajectories, 200 points, FP64: 7.3 ms
-    // with widths tuned on the first steps, which have few jumps, 4.9 with 4)
-    const bool narrow = !params[i].tile && b->hargs[i].NP <= kWaveLevels && wave_cols <= 8 * static_cast<int64_t>(cus);
-    if (narrow) b->tiles_per_inst[i] = 8;
-    if (b->tiles_per_inst[i] == 0) {
+    StepArgs& a = b->hargs[i];
+    aqt_ctx* c = ctxs[i];
+    int tile = b->tiles_per_inst[i];
+    if (!tile && a.NP <= kWaveLevels) tile = wave_batch_tile(wave_cols, cus);
+    if (!tile) {
       // heuristic: the largest allowed tile that still gives every CU several items
       int best = 1;
       for (int tq : kTQ)
-        if (batch_tq_ok(b->hargs[i].NP, tq, b->precision)) best = tq;
-      b->tiles_per_inst[i] = 8 * std::min(best, 4);
+        if (batch_tq_ok(a.NP, tq, b->precision)) best = tq;
+      tile = 8 * std::min(best, 4);
     }
-    StepArgs& a = b->hargs[i];
-    a.TQ = b->tiles_per_inst[i] / 8;
-    a.width = narrow ? 4 : 0;
-    a.tiles = narrow ? (a.K + 3) / 4 : (a.K + 8 * a.TQ - 1) / (8 * a.TQ);
-    aqt_ctx* c = ctxs[i];
-    const size_t need = static_cast<size_t>(a.tiles) * a.M * 2 * sizeof(double);
-    if (c->partial.reserve(need) != hipSuccess) return bail(b->fail(AQT_ENOMEM, "workspace allocation failed"));
+    for (;;) {
+      a.TQ = std::max(1, tile / 8);
+      a.width = tile < 8 ? tile : 0;
+      a.tiles = (a.K + tile - 1) / tile;
+      const hipError_t e = c->partial.reserve(static_cast<size_t>(a.tiles) * a.M * 2 * sizeof(double));
+      if (e == hipSuccess) break;
+      // a chosen width whose sums do not fit gives way to wider ones
+      if (params[i].tile || !batch_tq_ok(a.NP, 2 * a.TQ, b->precision))
+        return bail(b->fail(AQT_ENOMEM, "workspace allocation failed"));
+      (void)hipGetLastError();
+      tile = 16 * a.TQ;
+    }
+    b->tiles_per_inst[i] = std::max(8, tile);
     a.partial = c->partial.as<double>();
   }
   ClassSpans sp;

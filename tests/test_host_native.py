@@ -59,3 +59,8 @@ def test_packed_operands(library):
 def test_per_tile_sums_of_large_runs(library):
     """Memory limits at and below what the wider tiles need; the bound beyond which they are taken."""
     run_check(library, "plan_check")
+
+
+def test_batch_widths_up_to_32_levels(library):
+    """At the two limits of the rule, with and without autotuning, and explicit widths."""
+    run_check(library, "batch_check")
