@@ -84,7 +84,8 @@ typedef struct {
   uint64_t seed;            /* Philox key word 0                                    */
   uint64_t instance_id;     /* Philox key word 1                                    */
   uint64_t traj_offset;     /* trajectory ids are traj_offset .. traj_offset+K-1     */
-  int32_t tile;             /* trajectories per workgroup: 8, 16, 32, 40 or 64 (0: auto) */
+  int32_t tile;             /* trajectories per workgroup: 4 (up to 32 levels), 8, 16, 32, 40
+                               or 64 (0: auto)                                       */
   int32_t segment;          /* aqt_grad_pgs only: steps per checkpoint segment of the
                                adjoint sweep (0: automatic); ignored by aqt_run       */
 } aqt_run_params;
@@ -408,7 +409,8 @@ enum { AQT_BATCH_GRAPH = 1, AQT_BATCH_AUTOTUNE = 2 };
 AQT_API aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const aqt_run_params* params,
                                     const aqt_outputs* outs, int flags);
 AQT_API aqt_status aqt_batch_launch(aqt_batch* batch);
-/* Trajectories per workgroup tile chosen for each instance (host array [n]). */
+/* Trajectories per workgroup tile chosen for each instance (host array [n]); as params[i].tile
+ * each value asks for the same kernel again. */
 AQT_API aqt_status aqt_batch_tiles(const aqt_batch* batch, int32_t* tile_per_instance);
 AQT_API const char* aqt_batch_last_error(const aqt_batch* batch);
 AQT_API void aqt_batch_destroy(aqt_batch* batch);

@@ -1916,6 +1916,9 @@ int explicit_tq(int NP, int precision, int tile) {
   return tq_allowed(NP, tq, f64) ? tq : 0;
 }
 
+// Explicit tiles of half a column tile, as small launches up to kWaveLevels levels take them.
+bool explicit_narrow(int NP, int tile) { return tile == 4 && NP <= kWaveLevels; }
+
 // Split of K trajectories over the chip.  One-wavefront tiles: 8 trajectories while the
 // launch fits the chip at once (two wavefronts per SIMD), else 16; 4 of the 8 columns while that
 // fits, so that all crossings of a step are handled in one pass of four lane segments (32 levels FP32, us a step:
@@ -2020,6 +2023,11 @@ TilePlan run_plan(const aqt_ctx* ctx, const aqt_run_params* p) {
     return (ctx->NP <= kWaveLevels && partial_bytes(ctx, plan) > kMaxPartialBytes) ? single_width(p, 4) : plan;
   }
   TilePlan plan;
+  if (explicit_narrow(ctx->NP, p->tile)) {
+    plan.width = p->tile;
+    plan.add(1, (p->n_traj + p->tile - 1) / p->tile);
+    return plan;
+  }
   const int tq = explicit_tq(ctx->NP, p->precision, p->tile);
   if (tq) plan.add(tq, (p->n_traj + 8 * tq - 1) / (8 * tq));
   return plan;
@@ -2496,7 +2504,7 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
     if (params[i].record_capacity > 0 && !outs[i].jumps)
       return bail(b->fail(AQT_EINVAL, "record_capacity > 0 needs a jumps buffer"));
     if (outs[i].net_hist && outs[i].hist_hi < outs[i].hist_lo) return bail(b->fail(AQT_EINVAL, "hist_hi < hist_lo"));
-    if (params[i].tile && (params[i].tile % 8 || !batch_tq_ok(c->NP, params[i].tile / 8, b->precision)))
+    if (params[i].tile && !explicit_narrow(c->NP, params[i].tile) && (params[i].tile % 8 || !batch_tq_ok(c->NP, params[i].tile / 8, b->precision)))
       return bail(b->fail(AQT_EINVAL, "unsupported tile size in batch"));
     if (batch_class(c->NP, 1) < 0) return bail(b->fail(AQT_EINVAL, "unsupported level count in batch"));
     aqt_status s = check_step_decay(c, b->precision);
@@ -2581,12 +2589,12 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
       const hipError_t e = c->partial.reserve(static_cast<size_t>(a.tiles) * a.M * 2 * sizeof(double));
       if (e == hipSuccess) break;
       // a chosen width whose sums do not fit gives way to wider ones
-      if (params[i].tile || !batch_tq_ok(a.NP, 2 * a.TQ, b->precision))
+      tile *= 2;
+      if (params[i].tile || !batch_tq_ok(a.NP, tile / 8, b->precision))
         return bail(b->fail(AQT_ENOMEM, "workspace allocation failed"));
       (void)hipGetLastError();
-      tile = 16 * a.TQ;
     }
-    b->tiles_per_inst[i] = std::max(8, tile);
+    b->tiles_per_inst[i] = tile;
     a.partial = c->partial.as<double>();
   }
   ClassSpans sp;

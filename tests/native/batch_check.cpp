@@ -3,8 +3,6 @@
 
 namespace {
 
-constexpr int32_t kSmall = 8;
-
 // The widths of a batch of n instances of K trajectories each; *timed counts trajectory
 // launches during its creation.
 std::vector<int32_t> widths(int levels, int precision, int n, int64_t K, int flags, int tile = 0, size_t* timed = nullptr) {
@@ -30,18 +28,18 @@ std::vector<int32_t> widths(int levels, int precision, int n, int64_t K, int fla
   return t;
 }
 
-// Columns of 8 trajectories that a launch of the stub's 256 CUs takes: up to 8 a CU in tiles of
-// four (reported as the eight whose half they fill), up to 256 a CU in tiles of 8, else of 16.
+// Columns of 8 trajectories that a launch of the stub's 256 CUs takes: up to 8 a CU in tiles of 4,
+// up to 256 a CU in tiles of 8, else of 16.
 void chosen_widths() {
   for (int levels : {4, 16, 32})
     for (int precision : {AQT_FP64, AQT_FP32, AQT_BF16})
       for (int flags : {0, int(AQT_BATCH_AUTOTUNE)}) {
         size_t timed = 0;
-        CHECK(widths(levels, precision, 2, 8 * 1024, flags, 0, &timed)[0] == kSmall && timed == 0);
+        CHECK(widths(levels, precision, 2, 8 * 1024, flags, 0, &timed)[0] == 4 && timed == 0);
         CHECK(widths(levels, precision, 2, 8 * 1024 + 1, flags, 0, &timed)[0] == 8 && timed == 0);
         CHECK(widths(levels, precision, 2, 8 * 32768, flags, 0, &timed)[0] == 8 && timed == 0);
         CHECK(widths(levels, precision, 2, 8 * 32768 + 1, flags, 0, &timed)[0] == 16 && timed == 0);
-        for (int tile : {8, 16, 32, 64}) CHECK(widths(levels, precision, 2, 100, flags, tile)[0] == tile);
+        for (int tile : {4, 8, 16, 32, 64}) CHECK(widths(levels, precision, 2, 100, flags, tile)[0] == tile);
       }
 }
 
@@ -75,6 +73,35 @@ void widths_that_fit() {
   }
 }
 
+// The width that a batch reports is accepted as an explicit one, by batches and runs; 4 only up
+// to 32 levels, where it means that many.
+void width_of_four() {
+  for (int levels : {4, 32, 33, 256}) {
+    aqt_ctx* c = context_with_tables(levels, 4, 3);
+    aqt_run_params p{};
+    p.precision = AQT_FP64;
+    p.n_traj = 101;
+    p.tile = 4;
+    aqt_outputs o{};
+    const aqt_status want = levels <= 32 ? AQT_OK : AQT_EINVAL;
+    stub::calls.clear();
+    CHECK(aqt_run(c, &p, &o) == want);
+    for (const stub::Call& k : stub::calls)
+      if (k.name.find("k_trajectories") != std::string::npos) CHECK(k.grid.x == 26);
+    CHECK(stub::count("k_trajectories") == (levels <= 32 ? 1u : 0u));
+    aqt_batch* b = nullptr;
+    CHECK(aqt_batch_create(&b, &c, 1, &p, &o, 0) == want);
+    aqt_batch_destroy(b);
+    for (int tile : {1, 2, 3, 5, 6, 12, -4}) {
+      p.tile = tile;
+      CHECK(aqt_run(c, &p, &o) == AQT_EINVAL);
+      CHECK(aqt_batch_create(&b, &c, 1, &p, &o, 0) == AQT_EINVAL);
+      aqt_batch_destroy(b);
+    }
+    aqt_destroy(c);
+  }
+}
+
 // Above 32 levels autotuning times every width (the stub's clock stands still: the first).
 void timed_widths() {
   size_t timed = 0;
@@ -87,6 +114,7 @@ void timed_widths() {
 int main() {
   chosen_widths();
   widths_that_fit();
+  width_of_four();
   timed_widths();
   return 0;
 }
