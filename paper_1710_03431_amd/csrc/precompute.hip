@@ -1818,6 +1818,7 @@ aqt_status chfsi_chunk(aqt_ctx* ctx, Chfsi& c, const double* eZ, const std::vect
       if ((s = chfsi_solve(ctx, c, eZ, Ag, Bg, gidx, nconv, 1e-12)) != AQT_OK) return s;
       if (head[j] == 0) c.far[j] = 1;
     }
+    ctx->err.clear();   // the joint solve's message
   }
   if (s != AQT_OK) return s;
   // at s = 0 only the lowest levels converged: the next solve from this block starts

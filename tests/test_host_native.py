@@ -65,3 +65,8 @@ def test_batch_widths_up_to_32_levels(library):
     """At the two limits of the rule, with and without autotuning; explicit widths, among them the
     4 that small batches report."""
     run_check(library, "batch_check")
+
+
+def test_chain_heads_that_fail_together(library):
+    """In the first chunk and in a later one, whose first chain starts from the chunk before."""
+    run_check(library, "chains_check")
