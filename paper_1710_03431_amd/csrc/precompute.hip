@@ -1803,8 +1803,9 @@ aqt_status chfsi_chunk(aqt_ctx* ctx, Chfsi& c, const double* eZ, const std::vect
   s = chfsi_solve(ctx, c, eZ, Ag, Bg, gidx, nconv, 1e-12);
   if (s == AQT_ENUMERIC) {
     // a head that does not converge from a random block within its budget may do so from the
-    // head before it: one after another
-    if (g0 == 0) c.warm[0] = 0;
+    // head before it: one after another, the first from a random block (the failed solve may
+    // have left anything in its own)
+    c.warm[0] = 0;
     for (int j = 0; j < nc; ++j) {
       if (j > 0) {
         AQT_HIP(ctx, hipMemcpyAsync(c.at(c.X, j), c.at(c.X, j - 1), c.blk * 8, hipMemcpyDeviceToDevice, ctx->stream));

@@ -54,6 +54,7 @@ void failed_heads(int chunk) {
 
 int main() {
   failed_heads(0);
+  failed_heads(1);
 
   return 0;
 }
