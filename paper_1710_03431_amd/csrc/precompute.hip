@@ -1504,6 +1504,21 @@ struct Chfsi {
   std::vector<char> warm;   // per slot: X holds the Ritz block of a nearby grid point
   std::vector<char> far;    // per slot: ... of a grid point a chain length away (chain heads)
   double hub = 0.0;         // upper bound of the spectrum (Gershgorin)
+  bool reserve(size_t n) {   // blocks of n slots
+    const size_t kk = static_cast<size_t>(KB) * KB;
+    for (ScratchBuf* b : {&X, &Y1, &Y2, &W})
+      if (b->reserve(n * blk * 8) != hipSuccess) return false;
+    return part.reserve(n * ksplit * kk * 8) == hipSuccess && S.reserve(n * kk * 8) == hipSuccess &&
+           C.reserve(n * kk * 8) == hipSuccess && theta.reserve(n * KB * 8) == hipSuccess &&
+           res.reserve(n * KB * 8) == hipSuccess && ws.reserve(n * 2 * kk * 8) == hipSuccess &&
+           status.reserve(n * 4) == hipSuccess && act.reserve(n * 4) == hipSuccess &&
+           coef.reserve(n * (1 + kMaxFilterDegree) * sizeof(HxCoef)) == hipSuccess &&
+           info.reserve(n * 2 * 4) == hipSuccess && cl.reserve(n * 2 * KB * 4) == hipSuccess;
+  }
+  void release() {
+    for (ScratchBuf* b : {&X, &Y1, &Y2, &W, &part, &S, &C, &theta, &res, &ws, &status, &act, &coef, &info, &cl})
+      b->release();
+  }
   double* at(const ScratchBuf& b, int j) const { return b.as<double>() + static_cast<size_t>(j) * blk; }
 };
 
@@ -2058,17 +2073,18 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
     ch.ksplit = std::max(1, std::min(256, N / 256));
     ch.blk = static_cast<size_t>(KB) * N;
     const size_t kk = static_cast<size_t>(KB) * KB;
-    // slots (chains solved together): up to kMaxChains, within 8 GiB of workspace
+    // slots (chains solved together): up to kMaxChains, within 8 GiB of workspace, halved while
+    // they do not fit
     const size_t per_slot = (4 * ch.blk + static_cast<size_t>(ch.ksplit) * kk + 5 * kk + 2 * KB) * 8;
     ch.nb = static_cast<int>(std::max<size_t>(1, std::min<size_t>(max_chains(N), (size_t(8) << 30) / per_slot)));
+    while (!ch.reserve(ch.nb)) {
+      if (ch.nb == 1) return ctx->fail(AQT_ENOMEM, "subspace iteration workspace allocation failed");
+      (void)hipGetLastError();
+      ch.release();
+      scratch_flush();   // (else the halved requests are given the blocks just released)
+      ch.nb /= 2;
+    }
     const size_t nb = ch.nb;
-    if (ch.X.reserve(nb * ch.blk * 8) || ch.Y1.reserve(nb * ch.blk * 8) || ch.Y2.reserve(nb * ch.blk * 8) ||
-        ch.W.reserve(nb * ch.blk * 8) || ch.part.reserve(nb * ch.ksplit * kk * 8) || ch.S.reserve(nb * kk * 8) ||
-        ch.C.reserve(nb * kk * 8) || ch.theta.reserve(nb * KB * 8) || ch.res.reserve(nb * KB * 8) ||
-        ch.ws.reserve(nb * 2 * kk * 8) || ch.status.reserve(nb * 4) || ch.act.reserve(nb * 4) ||
-        ch.coef.reserve(nb * (1 + kMaxFilterDegree) * sizeof(HxCoef)) || ch.info.reserve(nb * 2 * 4) ||
-        ch.cl.reserve(nb * 2 * KB * 4))
-      return ctx->fail(AQT_ENOMEM, "subspace iteration workspace allocation failed");
     ch.h_theta.resize(nb * KB);
     ch.h_res.resize(nb * KB);
     ch.h_status.resize(nb);

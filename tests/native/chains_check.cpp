@@ -32,8 +32,8 @@ void failed_heads(int chunk) {
     if (failures) ++after;
     armed = armed || random == at;
   };
-  stub::on_download = [&](void* dst, const void*, size_t n) {
-    if (n == sizeof(int)) *static_cast<int*>(dst) = 1;   // the ground state of H(0) is not degenerate
+  stub::on_download = [&](void* dst, const void* src, size_t n) {
+    if (src == c->gs.p) *static_cast<int*>(dst) = 1;   // the ground state of H(0) is not degenerate
     if (armed && !failures && n == kSlots * sizeof(int)) {   // per-slot status of the small eigenproblems
       static_cast<int*>(dst)[0] = 1;
       ++failures;
@@ -50,11 +50,45 @@ void failed_heads(int chunk) {
   aqt_destroy(c);
 }
 
+// Chains solved together, by the random blocks they start from, within the memory there is.
+size_t chains_within(size_t room, aqt_status* status) {
+  aqt_ctx* c = iterative_context();
+  size_t random = 0;
+  stub::on_call = [&](const stub::Call& k) { random += k.name.find("k_random_block") != std::string::npos; };
+  stub::on_download = [&](void* dst, const void* src, size_t) {
+    if (src == c->gs.p) *static_cast<int*>(dst) = 1;
+  };
+  stub::peak = stub::used;
+  const size_t before = stub::used;
+  stub::limit = room ? before + room : size_t(288) << 30;
+  *status = aqt_precompute_ex(c, 200, 16, 1e-8, AQT_EIG_ITERATIVE);
+  stub::limit = size_t(288) << 30;
+  stub::on_call = nullptr;
+  stub::on_download = nullptr;
+  aqt_destroy(c);
+  return random;
+}
+
+// Block slots that do not fit are halved, down to one, before the call gives up.
+void fewer_slots_in_less_memory() {
+  aqt_status s;
+  size_t last = chains_within(0, &s), seen = 1;
+  CHECK(s == AQT_OK && last == kSlots);
+  for (size_t room = stub::peak - 1;; room -= 1 << 18) {
+    const size_t now = chains_within(room, &s);
+    if (s != AQT_OK) break;
+    CHECK(now == last || now == last / 2);
+    seen += now != last;
+    last = now;
+  }
+  CHECK(s == AQT_ENOMEM && last == 1 && seen == 7);
+}
+
 }  // namespace
 
 int main() {
   failed_heads(0);
   failed_heads(1);
-
+  fewer_slots_in_less_memory();
   return 0;
 }

@@ -4,7 +4,7 @@
 
 namespace stub {
 std::map<char*, size_t> live;
-size_t used = 0, limit = size_t(288) << 30;
+size_t used = 0, limit = size_t(288) << 30, peak = 0;
 size_t allocations = ~size_t(0);
 std::vector<Call> calls;
 std::function<void(const Call&)> on_call;
@@ -53,6 +53,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   *p = next_block;
   next_block += (n + 4096) & ~size_t(4095);
   used += n;
+  if (used > peak) peak = used;
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {

@@ -28,7 +28,7 @@ struct Call {
   void** args = nullptr;      // of a kernel, valid in on_call only
 };
 extern std::map<char*, size_t> live;          // allocated blocks
-extern size_t used, limit;                    // bytes, and the bytes there are
+extern size_t used, limit, peak;              // bytes, the bytes there are, the most in use
 extern size_t allocations;                    // that still succeed
 extern std::vector<Call> calls;               // in order
 extern std::function<void(const Call&)> on_call;

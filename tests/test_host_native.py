@@ -67,6 +67,7 @@ def test_batch_widths_up_to_32_levels(library):
     run_check(library, "batch_check")
 
 
-def test_chain_heads_that_fail_together(library):
-    """In the first chunk and in a later one, whose first chain starts from the chunk before."""
+def test_chains_of_the_iterative_eigensolver(library):
+    """Heads that fail together, in the first chunk and in a later one, whose first chain starts
+    from the chunk before; fewer chains in less memory."""
     run_check(library, "chains_check")
