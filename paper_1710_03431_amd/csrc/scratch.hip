@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "common.hpp"
@@ -22,9 +23,11 @@ struct DeviceCache {
 };
 std::mutex g_mutex;
 
-DeviceCache* caches() {
-  static DeviceCache* c = new DeviceCache[kMaxDevices];   // outlives every static destructor
-  return c;
+// The device's cache; null if there is none (device index, no host memory for it): blocks are
+// then allocated and freed as they come and go.
+DeviceCache* cache_of(int device) {
+  static DeviceCache* c = new (std::nothrow) DeviceCache[kMaxDevices];   // outlives every static destructor
+  return (c && device >= 0 && device < kMaxDevices) ? c + device : nullptr;
 }
 
 // Frees the oldest blocks until at most `limit` bytes are cached (the mutex is held).
@@ -42,9 +45,9 @@ void trim(DeviceCache& c, size_t limit) {
 
 hipError_t scratch_get(int device, size_t n, void** p, size_t* bytes) {
   n = std::max<size_t>((n + 255) & ~size_t(255), 256);
-  if (device >= 0 && device < kMaxDevices) {
+  if (DeviceCache* own = cache_of(device)) {
     std::lock_guard<std::mutex> lock(g_mutex);
-    DeviceCache& c = caches()[device];
+    DeviceCache& c = *own;
     size_t best = c.idle.size();
     for (size_t k = 0; k < c.idle.size(); ++k)
       if (c.idle[k].bytes >= n && c.idle[k].bytes <= 2 * n &&
@@ -69,9 +72,10 @@ hipError_t scratch_get(int device, size_t n, void** p, size_t* bytes) {
 }
 
 void scratch_put(int device, void* p, size_t bytes) {
-  if (device >= 0 && device < kMaxDevices && bytes <= kScratchCacheBytes) {
+  DeviceCache* own = cache_of(device);
+  if (own && bytes <= kScratchCacheBytes) {
     std::lock_guard<std::mutex> lock(g_mutex);
-    DeviceCache& c = caches()[device];
+    DeviceCache& c = *own;
     try {
       c.idle.push_back(Block{p, bytes});
       c.total += bytes;
@@ -85,15 +89,16 @@ void scratch_put(int device, void* p, size_t bytes) {
 
 void scratch_flush() {
   std::lock_guard<std::mutex> lock(g_mutex);
-  for (int d = 0; d < kMaxDevices; ++d) trim(caches()[d], 0);
+  for (int d = 0; d < kMaxDevices; ++d)
+    if (DeviceCache* c = cache_of(d)) trim(*c, 0);
 }
 
 void scratch_context(int device, int delta) {
-  if (device < 0 || device >= kMaxDevices) return;
+  DeviceCache* c = cache_of(device);
+  if (!c) return;
   std::lock_guard<std::mutex> lock(g_mutex);
-  DeviceCache& c = caches()[device];
-  c.contexts += delta;
-  if (c.contexts <= 0) trim(c, 0);
+  c->contexts += delta;
+  if (c->contexts <= 0) trim(*c, 0);
 }
 
 }  // namespace aqt

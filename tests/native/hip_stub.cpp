@@ -1,8 +1,10 @@
 #include "hip_stub.hpp"
 
 #include <cstring>
+#include <new>
 
 namespace stub {
+size_t host_allocations = ~size_t(0);
 std::map<char*, size_t> live;
 size_t used = 0, limit = size_t(288) << 30, peak = 0;
 size_t allocations = ~size_t(0);
@@ -16,6 +18,12 @@ std::map<const void*, std::string>& kernels() {
   static std::map<const void*, std::string> m;
   return m;
 }
+// The stub's own bookkeeping is not counted.
+struct Uncounted {
+  size_t n = host_allocations;
+  Uncounted() { host_allocations = ~size_t(0); }
+  ~Uncounted() { host_allocations = n; }
+};
 struct Config {
   dim3 grid, block;
   size_t shared;
@@ -26,7 +34,10 @@ void note(Call c) {
   c.args = nullptr;
   calls.push_back(c);
 }
-void note(const char* name, hipStream_t s = nullptr) { note(Call{name, s, dim3(1), nullptr}); }
+void note(const char* name, hipStream_t s = nullptr) {
+  Uncounted u;
+  note(Call{name, s, dim3(1), nullptr});
+}
 bool on_device(const void* p) {
   const char* c = static_cast<const char*>(p);
   auto it = live.upper_bound(const_cast<char*>(c));
@@ -45,8 +56,18 @@ void copy(void* dst, const void* src, size_t n) {
 
 using namespace stub;
 
+void* operator new(size_t n) {
+  if (!host_allocations) throw std::bad_alloc();
+  if (host_allocations != ~size_t(0)) --host_allocations;
+  if (void* p = std::malloc(n)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
+  Uncounted u;
   if (n > limit - used || !allocations) return hipErrorOutOfMemory;
   --allocations;
   live[next_block] = n;
@@ -58,6 +79,7 @@ hipError_t hipMalloc(void** p, size_t n) {
 }
 hipError_t hipFree(void* p) {
   if (!p) return hipSuccess;
+  Uncounted u;
   const auto it = live.find(static_cast<char*>(p));
   CHECK(it != live.end());
   used -= it->second;

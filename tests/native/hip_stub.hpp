@@ -29,7 +29,8 @@ struct Call {
 };
 extern std::map<char*, size_t> live;          // allocated blocks
 extern size_t used, limit, peak;              // bytes, the bytes there are, the most in use
-extern size_t allocations;                    // that still succeed
+extern size_t allocations;                    // on the device that still succeed
+extern size_t host_allocations;               // operator new of the code under check, likewise
 extern std::vector<Call> calls;               // in order
 extern std::function<void(const Call&)> on_call;
 extern std::function<void(void* dst, const void* src, size_t n)> on_download;
