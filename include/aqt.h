@@ -109,6 +109,13 @@ typedef struct {
  * for the default stream.  *out receives the context (NULL on failure). */
 AQT_API aqt_status aqt_create(aqt_ctx** out, int device, void* hip_stream);
 AQT_API void aqt_destroy(aqt_ctx* ctx);
+/* The synchronising calls (aqt_precompute, aqt_grad_pgs and what builds on them) keep their
+ * device workspaces for the next call, at most 16 GiB of idle ones per device, shared by its
+ * contexts.  They are given back when the device's last context is destroyed, when an
+ * allocation of this library needs the memory, and by this call (safe at any time, from any
+ * thread); an allocator beside this library, such as PyTorch's, cannot reclaim them itself.
+ * AQT_EINVAL if there is no such device. */
+AQT_API aqt_status aqt_release_workspaces(int device);
 AQT_API const char* aqt_last_error(const aqt_ctx* ctx);
 AQT_API int aqt_version(void);
 

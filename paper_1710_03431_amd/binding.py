@@ -20,7 +20,7 @@ FP64, FP32, BF16 = 0, 1, 2
 PRECISIONS = {"fp64": FP64, "fp32": FP32, "bf16": BF16}
 KIND_NAMES = ("relax", "excite", "dephase")
 
-EXPORTED = ("aqt_create", "aqt_destroy", "aqt_last_error", "aqt_version", "aqt_set_hamiltonian",
+EXPORTED = ("aqt_create", "aqt_destroy", "aqt_release_workspaces", "aqt_last_error", "aqt_version", "aqt_set_hamiltonian",
             "aqt_set_schedule", "aqt_set_bath", "aqt_precompute", "aqt_precompute_ex", "aqt_set_tables", "aqt_get_tables",
             "aqt_get_dims", "aqt_run", "aqt_grad_pgs", "aqt_set_lamb_shift", "aqt_get_lamb_shift",
             "aqt_set_bath_correlation", "aqt_set_bath_terms", "aqt_set_coupling", "aqt_get_channel_count",
@@ -83,6 +83,7 @@ def load_library(path: str = LIB_PATH):
     lib.aqt_create.argtypes = [C.POINTER(C.c_void_p), C.c_int, C.c_void_p]
     lib.aqt_destroy.argtypes = [ctx]
     lib.aqt_destroy.restype = None
+    lib.aqt_release_workspaces.argtypes = [C.c_int]
     lib.aqt_last_error.argtypes = [ctx]
     lib.aqt_last_error.restype = C.c_char_p
     lib.aqt_version.argtypes = []
@@ -138,6 +139,14 @@ def _iptr(a: Optional[np.ndarray]):
 
 def _f64(a) -> np.ndarray:
     return np.ascontiguousarray(np.asarray(a, dtype=np.float64))
+
+
+def release_workspaces(device: int = 0):
+    """Give the library's idle workspaces on a device (at most 16 GiB, kept between calls) back,
+    for instance before PyTorch needs the memory."""
+    st = load_library().aqt_release_workspaces(int(device))
+    if st != AQT_OK:
+        raise AqtError(st, f"no device {device}")
 
 
 class Engine:

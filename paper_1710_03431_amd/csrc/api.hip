@@ -126,6 +126,14 @@ void aqt_destroy(aqt_ctx* ctx) {
   aqt::scratch_context(device, -1);
 }
 
+aqt_status aqt_release_workspaces(int device) {
+  int count = 0;
+  if (hipGetDeviceCount(&count) != hipSuccess || count <= 0) return AQT_EHIP;
+  if (device < 0 || device >= count) return AQT_EINVAL;
+  aqt::scratch_release(device);
+  return AQT_OK;
+}
+
 const char* aqt_last_error(const aqt_ctx* ctx) { return ctx ? ctx->err.c_str() : "null context"; }
 
 aqt_status aqt_set_hamiltonian(aqt_ctx* ctx, int n_qubits, const double* h, const double* J) {

@@ -17,7 +17,7 @@ constexpr int kWave = 64;
 // ---------------------------------------------------------------- host -----
 // Idle device memory kept between calls for the workspaces of the synchronising entry points
 // (ScratchBuf), per device, shared by its contexts, at most kScratchCacheBytes; given back
-// when the device's last context is destroyed or an allocation fails.  Freeing and allocating
+// when the device's last context is destroyed, an allocation fails or the program asks.  Freeing and allocating
 // a workspace in every call costs more than the calls: memory that was just freed is cleared
 // before it can be handed out again, so a gradient step with 1 GB of workspace took 24 ms or
 // 60 to 88 ms depending on how far that clearing lagged.
@@ -25,6 +25,7 @@ constexpr size_t kScratchCacheBytes = size_t(16) << 30;
 hipError_t scratch_get(int device, size_t n, void** p, size_t* bytes);
 void scratch_put(int device, void* p, size_t bytes);   // the block must be idle
 void scratch_flush();                                  // frees every cached block
+void scratch_release(int device);                      // ... of one device
 void scratch_context(int device, int delta);           // a context came (+1) or went (-1)
 
 struct DevBuf {

@@ -93,6 +93,13 @@ void scratch_flush() {
     if (DeviceCache* c = cache_of(d)) trim(*c, 0);
 }
 
+void scratch_release(int device) {
+  DeviceCache* c = cache_of(device);
+  if (!c) return;
+  std::lock_guard<std::mutex> lock(g_mutex);
+  trim(*c, 0);
+}
+
 void scratch_context(int device, int delta) {
   DeviceCache* c = cache_of(device);
   if (!c) return;

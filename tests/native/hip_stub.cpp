@@ -1,6 +1,7 @@
 #include "hip_stub.hpp"
 
 #include <cstring>
+#include <mutex>
 #include <new>
 
 namespace stub {
@@ -18,8 +19,10 @@ std::map<const void*, std::string>& kernels() {
   static std::map<const void*, std::string> m;
   return m;
 }
-// The stub's own bookkeeping is not counted.
+// The stub's own bookkeeping is one thread's at a time and is not counted.
+std::recursive_mutex lock;
 struct Uncounted {
+  std::lock_guard<std::recursive_mutex> own{lock};
   size_t n = host_allocations;
   Uncounted() { host_allocations = ~size_t(0); }
   ~Uncounted() { host_allocations = n; }
@@ -30,6 +33,7 @@ struct Config {
   hipStream_t stream;
 } config;
 void note(Call c) {
+  std::lock_guard<std::recursive_mutex> own(lock);
   if (on_call) on_call(c);
   c.args = nullptr;
   calls.push_back(c);

@@ -1,6 +1,11 @@
 // The workspace cache (csrc/scratch.hip, ScratchBuf) behind a stubbed device allocator: every
 // block's true size is known here, so a block handed out below the size asked for is an error.
+#include <memory>
+#include <mutex>
 #include <random>
+#include <set>
+#include <thread>
+#include <vector>
 
 #include "ctx.hpp"
 #include "hip_stub.hpp"
@@ -50,27 +55,81 @@ void mixed_sizes() {
   }
 }
 
-// No host memory for the cache's own bookkeeping: contexts work without it.
-void no_host_memory() {
-  for (size_t good = 0;; ++good) {
-    aqt_ctx* c = nullptr;
-    stub::host_allocations = good;
-    const aqt_status s = aqt_create(&c, 0, nullptr);   // must not throw
-    stub::host_allocations = ~size_t(0);
-    if (s == AQT_OK) {
-      aqt_destroy(c);
-      if (good > 8) break;
-    } else {
-      CHECK(s == AQT_ENOMEM && !c);
+// Blocks stay within the cache's bound, oldest out first, and go back to the device when an
+// allocation needs them, when the program asks, and with the last context.
+void idle_blocks() {
+  aqt_ctx* c[2];
+  for (aqt_ctx*& k : c) CHECK(aqt_create(&k, 0, nullptr) == AQT_OK);
+  const size_t held = stub::used;   // by the contexts themselves
+  {
+    std::vector<std::unique_ptr<ScratchBuf>> bufs;
+    for (size_t k = 0; k < 20; ++k) {   // all out at once
+      bufs.push_back(std::make_unique<ScratchBuf>(c[k & 1]));
+      take(*bufs.back(), size_t(1) << 30);
     }
+    CHECK(stub::used - held == size_t(20) << 30);
   }
+  CHECK(stub::used - held == size_t(16) << 30);
+  stub::limit = stub::used;
+  {
+    ScratchBuf big(c[0]);   // fits no idle block
+    CHECK(big.reserve((size_t(16) << 30) + 1) != hipSuccess);
+    take(big, size_t(15) << 30);   // only with the idle blocks given back
+    CHECK(stub::used - held == size_t(15) << 30);
+  }
+  stub::limit = size_t(288) << 30;
+  CHECK(stub::used - held == size_t(15) << 30);
+  CHECK(aqt_release_workspaces(1) == AQT_EINVAL && aqt_release_workspaces(-1) == AQT_EINVAL);
+  CHECK(stub::used - held == size_t(15) << 30);
+  CHECK(aqt_release_workspaces(0) == AQT_OK);
+  CHECK(stub::used == held);
+  {
+    ScratchBuf b(c[0]);
+    take(b, 1 << 20);
+  }
+  aqt_destroy(c[0]);
+  CHECK(stub::used > (1 << 20));   // the other context keeps it
+  aqt_destroy(c[1]);
+  CHECK(stub::used == 0);
+}
+
+// Several threads with a context each; their blocks never overlap.
+void threads() {
+  std::mutex m;
+  std::set<char*> out;
+  std::vector<std::thread> pool;
+  for (int t = 0; t < 4; ++t)
+    pool.emplace_back([&, t] {
+      aqt_ctx ctx;
+      aqt::scratch_context(0, 1);
+      std::mt19937 rng(t);
+      for (int k = 0; k < 2000; ++k) {
+        ScratchBuf a(&ctx), b(&ctx);
+        CHECK(a.reserve(1 + rng() % (1 << 20)) == hipSuccess && b.reserve(1 + rng() % (1 << 20)) == hipSuccess);
+        if (k & 1) a.swap(b);
+        {
+          std::lock_guard<std::mutex> lock(m);
+          CHECK(out.insert(a.as<char>()).second && out.insert(b.as<char>()).second);
+        }
+        std::this_thread::yield();
+        {
+          std::lock_guard<std::mutex> lock(m);
+          out.erase(a.as<char>());
+          out.erase(b.as<char>());
+        }
+      }
+      aqt::scratch_context(0, -1);
+    });
+  for (std::thread& t : pool) t.join();
+  CHECK(stub::used == 0);
 }
 
 }  // namespace
 
 int main() {
-  no_host_memory();
   mixed_sizes();
+  idle_blocks();
+  threads();
   std::puts("ok");
   return 0;
 }

@@ -46,8 +46,14 @@ def run_check(library, name):
 
 
 def test_workspace_cache_never_hands_out_a_smaller_block(library):
-    """Mixed sizes and both parities of the block solver's buffer exchange."""
+    """Mixed sizes and both parities of the block solver's buffer exchange; the bound, an allocation
+    that needs the idle blocks, the release call, the last context, several threads."""
     run_check(library, "scratch_check")
+
+
+def test_create_without_host_memory(library):
+    """Each host allocation of aqt_create failing in turn."""
+    run_check(library, "nomem_check")
 
 
 def test_packed_operands(library):
