@@ -248,9 +248,8 @@ __device__ __forceinline__ void wg_tridiagonalize(double* A, int N, int lda, Sh&
 // stale lower triangle and correct the product by the held-back updates (two dot
 // products each).  The product: row sums by wavefront reductions, the transposed
 // half accumulated per lane and combined across wavefronts in a fixed order.  Per
-// two steps one read-write and one read-only pass over the lower triangle: a quarter
-// of the traffic of wg_tridiagonalize (which reads the full matrix for the product
-// and reads and writes it for the update, every step).
+// two steps one read-write and one read-only pass, as in wg_tridiagonalize, but over the
+// lower triangle alone: half its traffic.
 template <class Sh>
 __device__ __forceinline__ void wg_tridiagonalize_streamed(double* A, int N, int lda, Sh& sh) {
   constexpr int NT = (Sh::kMax + kWave - 1) / kWave;   // column slots per lane

@@ -1043,7 +1043,10 @@ constexpr int kMaxFilterDegree = 256;  // Chebyshev filter degree, at most
 // neighbour (2 to 3).  Up to 8192 states an iteration's time is that of the small dense
 // eigenproblems, one workgroup per slot, so many short chains cost least (12 qubits, 60
 // points: 317 ms with 7 chains of 8, 116 with 30 of 2); beyond, the block products' memory
-// traffic binds and long chains do.
+// traffic binds and long chains do.  32 levels, ms with up to 16 chains of 8 and heads one after
+// another, then with this rule and joint heads: 10 qubits, 100 points 221, 35; 11 qubits, 60
+// points 289, 106, 300 points 906, 433; 12 qubits, 300 points 1039, 285; 13 qubits, 60 points 573,
+// 163, 200 points 1049, 336; above the line 14 qubits, 24 points 473, 423, 60 points 696, 477.
 constexpr int kMaxChains = 64;
 constexpr int max_chains(int N) { return N <= 8192 ? kMaxChains : 16; }
 constexpr int chain_min_run(int N) { return N <= 8192 ? 2 : 8; }

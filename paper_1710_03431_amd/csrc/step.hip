@@ -1932,7 +1932,10 @@ bool explicit_narrow(int NP, int tile) { return tile == 4 && NP <= kWaveLevels; 
 // binds), so what counts is not to pay for idle columns: 10^4 trajectories (4.9 columns a
 // CU) take 3 + 2 (46.2 us a step) instead of three rounds of 2 (56.8); FP32 and BF16 gain
 // from width up to 5 (4096 FP32 trajectories on 256 tiles of 16: 11.1 us instead of 19.1 on 128
-// tiles of 32).
+// tiles of 32).  At 128 levels a step of 1 to 5 columns takes, in the same unit, FP64 44, 69, 94
+// (up to 3), FP32 34, 49, 62, 74, 87 and BF16 26, 35, 41, 47, 55: for up to 8 columns a CU the
+// sets chosen here are the best by these in FP32 and BF16 (or within 2%), and in FP64 but for 6 and
+// 8 columns (2 + 2 + 2 instead of 3 + 3: 10%, 7%).
 TilePlan plan_tiles(int NP, int precision, int64_t K, int cus) {
   const int64_t cols = (K + 7) / 8;
   const bool f64 = precision == AQT_FP64;
@@ -2363,8 +2366,10 @@ std::vector<BatchItem> build_items(const std::vector<StepArgs>& args, ClassSpans
 // Trajectories a tile of a batch's instances up to kWaveLevels levels, from the 8-trajectory
 // columns of all of them.  A one-wavefront tile handles its crossings one pass after another, so
 // what ends a batch is the jumps of its longest anneals, and narrow tiles spread them.  4 (half
-// the columns, as in plan_tiles) up to 8 columns a CU: 12 instances of 1000 trajectories, 200
-// points, FP64 take 4.9 ms with 4 and 7.3 with 8.  8 up to 256 a CU, 16 beyond (ms with 8, 16
+// the columns, as in plan_tiles) up to 8 columns a CU: 24 instances, 200 points, with 4 and with 8
+// take 5.1 and 9.0 ms in FP64 at one column a CU, 6.1 and 10.1 at 8, FP32 3.7 and 6.3, 4.0 and 6.7
+// (at 16 a CU 4 is still ahead, 7.4 to 10.4; the line is as far as small batches were tried when
+// it was drawn).  8 up to 256 a CU, 16 beyond (ms with 8, 16
 // and 32; 24 instances, 24 a CU: FP64 11.3, 18.6, 32.9, FP32 7.1, 12.4, 22.4; 60 instances, 240 a
 // CU, 100 points: 58.9, 62.8, 74.6 and 34.7, 37.5, 43.7; 24 instances, 469 a CU: 74.3, 69.3, 71.6
 // and 43.4, 40.7, 44.7).  Timing the first steps, which have few jumps, picks wider tiles than
