@@ -193,7 +193,9 @@ AQT_API aqt_status aqt_run(aqt_ctx* ctx, const aqt_run_params* params, const aqt
  * serving loops, harnesses that forbid hipMalloc): aqt_run without any allocation.  The
  * per-tile observable sums go to a fixed buffer of AQT_NOALLOC_SCRATCH_BYTES in device
  * memory, one per device, set up by aqt_create and held until the process ends.
- * Same arguments, outputs, kernels, results and stream ordering as aqt_run; the caller
+ * Same arguments, outputs, kernels, results and stream ordering as aqt_run (where the sums
+ * of the tile width that aqt_run chooses exceed the buffer, the widest tile: the same
+ * trajectories, their sums grouped differently and equal to rounding); the caller
  * still provides every output buffer.  Calls no hipMalloc, hipFree or allocating
  * library routine.  Errors (nothing enqueued):
  *   AQT_ESTATE  the step operands of params->precision are not resident (aqt_run packs
