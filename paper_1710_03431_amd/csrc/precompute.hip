@@ -2076,10 +2076,11 @@ aqt_status precompute_tables(aqt_ctx* ctx, int M, int n, double tol, int method,
     ch.ksplit = std::max(1, std::min(256, N / 256));
     ch.blk = static_cast<size_t>(KB) * N;
     const size_t kk = static_cast<size_t>(KB) * KB;
-    // slots (chains solved together): up to kMaxChains, within 8 GiB of workspace, halved while
-    // they do not fit
+    // slots (chains solved together): as many as a chunk has chains, up to kMaxChains, within 8 GiB
+    // of workspace, halved while they do not fit
     const size_t per_slot = (4 * ch.blk + static_cast<size_t>(ch.ksplit) * kk + 5 * kk + 2 * KB) * 8;
     ch.nb = static_cast<int>(std::max<size_t>(1, std::min<size_t>(max_chains(N), (size_t(8) << 30) / per_slot)));
+    ch.nb = std::max(1, std::min(ch.nb, std::min(M, Gc) / chain_min_run(N)));
     while (!ch.reserve(ch.nb)) {
       if (ch.nb == 1) return ctx->fail(AQT_ENOMEM, "subspace iteration workspace allocation failed");
       (void)hipGetLastError();

@@ -51,7 +51,7 @@ void failed_heads(int chunk) {
 }
 
 // Chains solved together, by the random blocks they start from, within the memory there is.
-size_t chains_within(size_t room, aqt_status* status) {
+size_t chains_within(size_t room, aqt_status* status, int points = 200) {
   aqt_ctx* c = iterative_context();
   size_t random = 0;
   stub::on_call = [&](const stub::Call& k) { random += k.name.find("k_random_block") != std::string::npos; };
@@ -61,7 +61,7 @@ size_t chains_within(size_t room, aqt_status* status) {
   stub::peak = stub::used;
   const size_t before = stub::used;
   stub::limit = room ? before + room : size_t(288) << 30;
-  *status = aqt_precompute_ex(c, 200, 16, 1e-8, AQT_EIG_ITERATIVE);
+  *status = aqt_precompute_ex(c, points, 16, 1e-8, AQT_EIG_ITERATIVE);
   stub::limit = size_t(288) << 30;
   stub::on_call = nullptr;
   stub::on_download = nullptr;
@@ -84,11 +84,24 @@ void fewer_slots_in_less_memory() {
   CHECK(s == AQT_ENOMEM && last == 1 && seen == 7);
 }
 
+// A short grid takes the slots of its own chains (of two points and more) alone.
+void slots_of_a_short_grid() {
+  aqt_status s;
+  size_t peak[2];
+  for (int k = 0; k < 2; ++k) {
+    const size_t before = stub::used;
+    CHECK(chains_within(0, &s, k ? 128 : 8) == (k ? 64 : 4) && s == AQT_OK);
+    peak[k] = stub::peak - before;
+  }
+  CHECK(8 * peak[0] < peak[1]);
+}
+
 }  // namespace
 
 int main() {
   failed_heads(0);
   failed_heads(1);
   fewer_slots_in_less_memory();
+  slots_of_a_short_grid();
   return 0;
 }

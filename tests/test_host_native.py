@@ -75,5 +75,5 @@ def test_batch_widths_up_to_32_levels(library):
 
 def test_chains_of_the_iterative_eigensolver(library):
     """Heads that fail together, in the first chunk and in a later one, whose first chain starts
-    from the chunk before; fewer chains in less memory."""
+    from the chunk before; fewer chains in less memory; the workspace of a short grid."""
     run_check(library, "chains_check")
