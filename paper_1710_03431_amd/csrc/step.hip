@@ -2195,6 +2195,7 @@ struct aqt_batch {
   std::vector<aqt::StepArgs> hargs;
   std::vector<int> tiles_per_inst;        // trajectories per workgroup tile chosen per instance
   aqt::DevBuf dargs, ditems, dcounter;
+  aqt::DevBuf sums;                       // per-tile sums of every instance
   int n_items = 0;
   int class_off[20] = {};                 // items of each (levels, tile) group
   int class_cnt[20] = {};
@@ -2576,9 +2577,8 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
   for (int i = 0; i < n; ++i)
     if (b->hargs[i].NP <= kWaveLevels) wave_cols += (b->hargs[i].K + 7) / 8;
   for (int i = 0; i < n; ++i) {
-    StepArgs& a = b->hargs[i];
-    aqt_ctx* c = ctxs[i];
-    int tile = b->tiles_per_inst[i];
+    const StepArgs& a = b->hargs[i];
+    int& tile = b->tiles_per_inst[i];
     if (!tile && a.NP <= kWaveLevels) tile = wave_batch_tile(wave_cols, cus);
     if (!tile) {
       // heuristic: the largest allowed tile that still gives every CU several items
@@ -2587,21 +2587,32 @@ aqt_status aqt_batch_create(aqt_batch** out, aqt_ctx* const* ctxs, int n, const 
         if (batch_tq_ok(a.NP, tq, b->precision)) best = tq;
       tile = 8 * std::min(best, 4);
     }
-    for (;;) {
+  }
+  // per-tile sums of every instance, in one buffer of the batch: the contexts' own ones move with
+  // their runs.  Chosen widths whose sums do not fit give way to wider ones.
+  std::vector<size_t> sums(n);
+  for (;;) {
+    size_t need = 0;
+    for (int i = 0; i < n; ++i) {
+      StepArgs& a = b->hargs[i];
+      const int tile = b->tiles_per_inst[i];
       a.TQ = std::max(1, tile / 8);
       a.width = tile < 8 ? tile : 0;
       a.tiles = (a.K + tile - 1) / tile;
-      const hipError_t e = c->partial.reserve(static_cast<size_t>(a.tiles) * a.M * 2 * sizeof(double));
-      if (e == hipSuccess) break;
-      // a chosen width whose sums do not fit gives way to wider ones
-      tile *= 2;
-      if (params[i].tile || !batch_tq_ok(a.NP, tile / 8, b->precision))
-        return bail(b->fail(AQT_ENOMEM, "workspace allocation failed"));
-      (void)hipGetLastError();
+      sums[i] = need;
+      need += (static_cast<size_t>(a.tiles) * a.M * 2 * sizeof(double) + 255) & ~size_t(255);
     }
-    b->tiles_per_inst[i] = tile;
-    a.partial = c->partial.as<double>();
+    if (b->sums.reserve(need) == hipSuccess) break;
+    (void)hipGetLastError();
+    bool wider = false;
+    for (int i = 0; i < n; ++i)
+      if (!params[i].tile && batch_tq_ok(b->hargs[i].NP, 2 * b->tiles_per_inst[i] / 8, b->precision)) {
+        b->tiles_per_inst[i] *= 2;
+        wider = true;
+      }
+    if (!wider) return bail(b->fail(AQT_ENOMEM, "workspace allocation failed"));
   }
+  for (int i = 0; i < n; ++i) b->hargs[i].partial = reinterpret_cast<double*>(b->sums.as<char>() + sums[i]);
   ClassSpans sp;
   std::vector<BatchItem> items = build_items(b->hargs, &sp);
   b->n_items = static_cast<int>(items.size());

@@ -102,6 +102,33 @@ void width_of_four() {
   }
 }
 
+// A batch's per-tile sums are its own: a larger run of a member (also of one that is in the batch
+// twice) frees nothing that the batch's launches use.
+void sums_of_its_own() {
+  aqt_ctx* c[3] = {context_with_tables(16, 4, 50), context_with_tables(64, 4, 50), nullptr};
+  c[2] = c[0];
+  aqt_run_params p[3]{};
+  aqt_outputs o[3]{};
+  for (int k = 0; k < 3; ++k) {
+    p[k].precision = AQT_FP64;
+    p[k].n_traj = 100 + 1000 * k;
+  }
+  aqt_batch* b = nullptr;
+  CHECK(aqt_batch_create(&b, c, 3, p, o, 0) == AQT_OK);
+  const auto live = stub::live;
+  for (int k = 0; k < 2; ++k)
+    for (int64_t K : {1000, 100000}) {
+      p[k].n_traj = K;
+      CHECK(aqt_run(c[k], &p[k], &o[k]) == AQT_OK);
+    }
+  size_t gone = 0;
+  for (const auto& l : live) gone += !stub::live.count(l.first);
+  CHECK(gone == 0);
+  CHECK(aqt_batch_launch(b) == AQT_OK);
+  aqt_batch_destroy(b);
+  for (int k = 0; k < 2; ++k) aqt_destroy(c[k]);
+}
+
 // Above 32 levels autotuning times every width (the stub's clock stands still: the first).
 void timed_widths() {
   size_t timed = 0;
@@ -115,6 +142,7 @@ int main() {
   chosen_widths();
   widths_that_fit();
   width_of_four();
+  sums_of_its_own();
   timed_widths();
   return 0;
 }

@@ -53,3 +53,32 @@ def test_width_of_four_is_refused_above_32_levels():
     with pytest.raises(AqtError) as e:
         eng.run(64, "fp64", tile=4)
     assert e.value.status == AQT_EINVAL
+
+
+def test_launches_around_larger_runs_of_the_members():
+    """A member's own runs, larger and in flight beside the batch, leave its sums alone."""
+    from paper_1710_03431_amd.binding import Batch, Engine
+    import torch
+    inst = W.ring_instance(5, 35, n_grid=101)
+    engines = []
+    for _ in range(2):
+        eng = Engine(0, stream=torch.cuda.Stream())
+        eng.set_instance(inst)
+        eng.precompute(inst.n_grid, inst.levels)
+        engines.append(eng)
+    torch.cuda.synchronize()
+    b = Batch(engines, [dict(n_traj=500, seed=3, instance_id=k) for k in range(2)], precision="fp64", graph=True,
+              autotune=False)
+    b.launch()
+    first = b.results()
+    outs = engines[1].alloc_outputs(40000)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        b.launch()
+        engines[1].run_into(outs, 40000, "fp64", seed=9)
+    torch.cuda.synchronize()
+    again = b.results()
+    for x, y in zip(first, again):
+        np.testing.assert_array_equal(x["pgs_sum"], y["pgs_sum"])
+        np.testing.assert_array_equal(x["pgs_sumsq"], y["pgs_sumsq"])
+        np.testing.assert_array_equal(4 * x["jump_totals"], y["jump_totals"])

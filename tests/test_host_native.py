@@ -69,7 +69,7 @@ def test_per_tile_sums_of_large_runs(library):
 
 def test_batch_widths_up_to_32_levels(library):
     """At the two limits of the rule, with and without autotuning; explicit widths, among them the
-    4 that small batches report."""
+    4 that small batches report; the batch's per-tile sums."""
     run_check(library, "batch_check")
 
 
